@@ -1026,20 +1026,25 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs<T> f) {
     }
 }
 
-// Reverse-pair index: for pair p = (i -> j, n) find q = (j -> i, -n) in the
-// list of j (8 atoms x 32 lanes per 256-thread block).
+// Reverse-pair index: for pair p = (i -> j, n) find the first q = (j -> i,
+// -n) in the list of j.  REV_LANES lanes serve one pair and compare
+// consecutive entries of j's list, so a step reads one or two cache lines
+// per pair (one lane per pair walked 64 lists at once: 21 us for the
+// 15,840-atom list, 1.13 ms for the 1,024,000-atom one).
+constexpr int REV_LANES = 8;
 __global__ __launch_bounds__(256) void reverse_kernel(const int* __restrict__ offsets, const int* __restrict__ nbr_j,
                                                       const int* __restrict__ shift, int N, int P, int* rev,
                                                       int* err) {
+    constexpr int G = REV_LANES;
     const int a = blockIdx.x * 8 + static_cast<int>(threadIdx.x) / 32;
-    const int s0 = threadIdx.x % 32;
+    const int s0 = static_cast<int>(threadIdx.x % 32) / G, sub = threadIdx.x % G, lane = threadIdx.x % WAVE;
     if (a >= N) return;
     const int b = offsets[a], e = offsets[a + 1];
     if (b < 0 || e < b || e > P) {
-        if (s0 == 0) atomicOr(err, ERR_NEIGH);
+        if (s0 == 0 && sub == 0) atomicOr(err, ERR_NEIGH);
         return;
     }
-    for (int p = b + s0; p < e; p += 32) {
+    for (int p = b + s0; p < e; p += 32 / G) {
         const int j = nbr_j[p];
         const int sh = shift[p];
         int found = -1;
@@ -1048,11 +1053,21 @@ __global__ __launch_bounds__(256) void reverse_kernel(const int* __restrict__ of
                             (((-unpack_shift(sh, 2)) & 0xFF) << 16);
             const int jb = offsets[j], je = offsets[j + 1];
             if (jb >= 0 && je >= jb && je <= P)
-                for (int qq = jb; qq < je; ++qq)
-                    if (nbr_j[qq] == a && (shift[qq] & 0xFFFFFF) == neg) { found = qq; break; }
+                for (int q0 = jb; q0 < je && found < 0; q0 += 2 * G) {
+                    const int qa = q0 + sub, qb = qa + G;
+                    const int na = qa < je ? nbr_j[qa] : -1, nb = qb < je ? nbr_j[qb] : -1;
+                    const bool ha = na == a && (shift[qa] & 0xFFFFFF) == neg;
+                    const bool hb = nb == a && (shift[qb] & 0xFFFFFF) == neg;
+                    const unsigned ma = static_cast<unsigned>(__ballot(ha) >> (lane - sub)) & ((1u << G) - 1u);
+                    const unsigned mb = static_cast<unsigned>(__ballot(hb) >> (lane - sub)) & ((1u << G) - 1u);
+                    if (ma) found = q0 + __ffs(ma) - 1;
+                    else if (mb) found = q0 + G + __ffs(mb) - 1;
+                }
         }
-        rev[p] = found;
-        if (found < 0) atomicOr(err, ERR_NEIGH);
+        if (sub == 0) {
+            rev[p] = found;
+            if (found < 0) atomicOr(err, ERR_NEIGH);
+        }
     }
 }
 

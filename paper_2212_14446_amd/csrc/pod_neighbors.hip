@@ -26,6 +26,11 @@ namespace pod {
 namespace {
 
 constexpr int NB_THREADS = 256;
+// Lanes per atom of the search.  List and reverse index together, 8 / 16 / 32
+// lanes: 128 atoms 128 / 111 / 107 us, 15,840 atoms 164 / 151 / 151 us,
+// 1,024,000 atoms (FP32) 2.48 / 2.56 / 2.77 ms (one thread per atom: 303, 324
+// us and 4.25 ms), so one width serves the whole range.
+constexpr int NB_LANES = 16;
 constexpr int NB_MAX_WRAP = 1 << 20;   // |lattice vectors| between an atom and its home cell
 
 __device__ __forceinline__ int floor_div(int a, int b) {
@@ -93,92 +98,18 @@ __global__ __launch_bounds__(NB_THREADS) void order_kernel(int N, const int* __r
 
 // FILL = false: number of neighbours of every atom into cnt[i];
 // FILL = true: the neighbours themselves from offsets[i] on (same order).
-// The rows of a workgroup's atoms are one contiguous range of the list:
-// when it fits the workgroup's LDS (FILL_CAP entries) the rows are built
-// there and copied out with consecutive threads on consecutive entries
-// (each thread's own row would otherwise be written with one scattered
-// 4-byte store per entry and lane).
-constexpr int FILL_CAP = 4096;
-constexpr int FILL_THREADS = 128;   // workgroup of the fill pass
-
-// The search of one atom; with `stage`, its row goes to stage[out ..] and
-// stage[FILL_CAP + out ..] (LDS) instead of nbr_j / shift.
-template <bool FILL>
-__device__ __forceinline__ void search_atom(int i, const NbGeom& g, const int* __restrict__ key,
-                                            const int* __restrict__ sidx, const int* __restrict__ start,
-                                            const int* __restrict__ end, const double* __restrict__ wpos,
-                                            const double* __restrict__ spos, const int* __restrict__ wrap,
-                                            long* __restrict__ cnt, const int* __restrict__ offsets,
-                                            int* __restrict__ nbr_j, int* __restrict__ shift, int* err,
-                                            int* stage) {
-    const int b = key[i];
-    const int ci[3] = {b % g.nb[0], (b / g.nb[0]) % g.nb[1], b / (g.nb[0] * g.nb[1])};
-    const double ri[3] = {wpos[3 * i], wpos[3 * i + 1], wpos[3 * i + 2]};
-    int n = 0;
-    const int out = FILL ? offsets[i] : 0;
-    const int room = FILL ? offsets[i + 1] - out : 0;
-    for (int dz = -g.ns[2]; dz <= g.ns[2]; ++dz)
-        for (int dy = -g.ns[1]; dy <= g.ns[1]; ++dy)
-            for (int dx = -g.ns[0]; dx <= g.ns[0]; ++dx) {
-                const int bp[3] = {ci[0] + dx, ci[1] + dy, ci[2] + dz};
-                int S[3] = {0, 0, 0}, bb[3] = {bp[0], bp[1], bp[2]};
-                if (g.periodic) {
-                    for (int d = 0; d < 3; ++d) {
-                        S[d] = floor_div(bp[d], g.nb[d]);
-                        bb[d] = bp[d] - S[d] * g.nb[d];
-                    }
-                } else if (bp[0] < 0 || bp[0] >= g.nb[0] || bp[1] < 0 || bp[1] >= g.nb[1] || bp[2] < 0 ||
-                           bp[2] >= g.nb[2]) {
-                    continue;
-                }
-                const bool home = S[0] == 0 && S[1] == 0 && S[2] == 0;
-                double q[3];
-                for (int e = 0; e < 3; ++e) {
-                    double o = 0.0;
-                    if (g.periodic)
-                        o = __dadd_rn(__dadd_rn(__dmul_rn(S[0], g.a[0 * 3 + e]), __dmul_rn(S[1], g.a[1 * 3 + e])),
-                                      __dmul_rn(S[2], g.a[2 * 3 + e]));
-                    q[e] = __dsub_rn(ri[e], o);
-                }
-                const int bin = (bb[2] * g.nb[1] + bb[1]) * g.nb[0] + bb[0];
-                const int k1 = end[bin];
-                for (int k = start[bin]; k < k1; ++k) {
-                    // explicit roundings: the count and fill passes take the
-                    // same decision for every pair
-                    const double d0 = __dsub_rn(spos[3 * k], q[0]);
-                    const double d1 = __dsub_rn(spos[3 * k + 1], q[1]);
-                    const double d2 = __dsub_rn(spos[3 * k + 2], q[2]);
-                    const double r2 = __dadd_rn(__dadd_rn(__dmul_rn(d0, d0), __dmul_rn(d1, d1)), __dmul_rn(d2, d2));
-                    if (!(r2 < g.rl2)) continue;
-                    const int j = sidx[k];
-                    if (home && j == i) continue;
-                    if (FILL) {
-                        if (n >= room) {   // the count pass saw fewer pairs: never write past the row
-                            atomicOr(err, ERR_NEIGH);
-                            continue;
-                        }
-                        // image in the caller's coordinates: r_ij = pos_j + n a - pos_i
-                        const int n0 = S[0] - wrap[3 * j] + wrap[3 * i];
-                        const int n1 = S[1] - wrap[3 * j + 1] + wrap[3 * i + 1];
-                        const int n2 = S[2] - wrap[3 * j + 2] + wrap[3 * i + 2];
-                        if (n0 < -127 || n0 > 127 || n1 < -127 || n1 > 127 || n2 < -127 || n2 > 127)
-                            atomicOr(err, ERR_NEIGH);   // beyond the signed-byte shift
-                        const int sh = (n0 & 0xFF) | ((n1 & 0xFF) << 8) | ((n2 & 0xFF) << 16);
-                        if (stage) {
-                            stage[out + n] = j;
-                            stage[FILL_CAP + out + n] = sh;
-                        } else {
-                            nbr_j[out + n] = j;
-                            shift[out + n] = sh;
-                        }
-                    }
-                    ++n;
-                }
-            }
-    if (!FILL) cnt[i] = n;
-}
-
-template <bool FILL>
+//
+// G lanes serve one atom.  The bins of one (y, z) row around the atom are
+// consecutive in bin order, so a row's candidates are one range of the
+// sorted atoms (one range per periodic image when the row wraps): lane s of
+// the group looks up the range of segment s, then the group walks the
+// segments together, G candidates per step, and a ballot gives every
+// accepted candidate its place behind the earlier ones -- the order of a
+// serial scan.  One thread per atom (the former split) left 247 wavefronts
+// on the chip for 15,840 atoms, each serially waiting on ~200 dependent
+// candidate loads.
+// (Count and fill pass for 15,840 atoms: 95 + 118 us before.)
+template <bool FILL, int G>
 __global__ __launch_bounds__(NB_THREADS) void search_kernel(int N, NbGeom g, const int* __restrict__ key,
                                                             const int* __restrict__ sidx,
                                                             const int* __restrict__ start, const int* __restrict__ end,
@@ -187,29 +118,100 @@ __global__ __launch_bounds__(NB_THREADS) void search_kernel(int N, NbGeom g, con
                                                             const int* __restrict__ wrap, long* __restrict__ cnt,
                                                             const int* __restrict__ offsets, int* __restrict__ nbr_j,
                                                             int* __restrict__ shift, int* err) {
-    extern __shared__ int sfill[];   // FILL: [FILL_CAP] neighbour indices, [FILL_CAP] shifts
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int base = 0, total = 0;
-    bool staged = false;
-    if (FILL) {
-        const int i0 = min(static_cast<int>(blockIdx.x * blockDim.x), N);
-        const int i1 = min(i0 + static_cast<int>(blockDim.x), N);
-        base = offsets[i0];
-        total = offsets[i1] - base;
-        staged = total >= 0 && total <= FILL_CAP;
-    }
-    if (i < N) search_atom<FILL>(i, g, key, sidx, start, end, wpos, spos, wrap, cnt, offsets, nbr_j, shift, err,
-                                 staged ? sfill - base : nullptr);
-    if (FILL && staged) {
-        __syncthreads();
-        for (int t = threadIdx.x; t < total; t += blockDim.x) {
-            nbr_j[base + t] = sfill[t];
-            shift[base + t] = sfill[FILL_CAP + t];
+    static_assert(G == 8 || G == 16 || G == 32, "lanes per atom");
+    constexpr unsigned GM = G == 32 ? 0xFFFFFFFFu : (1u << G) - 1u;
+    const int lane = threadIdx.x % WAVE, sub = threadIdx.x % G;
+    const int i = blockIdx.x * (NB_THREADS / G) + static_cast<int>(threadIdx.x) / G;
+    if (i >= N) return;   // whole groups
+    const int b = key[i];
+    const int ci[3] = {b % g.nb[0], (b / g.nb[0]) % g.nb[1], b / (g.nb[0] * g.nb[1])};
+    const double ri[3] = {wpos[3 * i], wpos[3 * i + 1], wpos[3 * i + 2]};
+    int wi[3] = {0, 0, 0};
+    if (FILL) { wi[0] = wrap[3 * i]; wi[1] = wrap[3 * i + 1]; wi[2] = wrap[3 * i + 2]; }
+    int n = 0;
+    const int out = FILL ? offsets[i] : 0;
+    const int room = FILL ? offsets[i + 1] - out : 0;
+    // segments of a row: one per image of the row it crosses
+    const int x0 = ci[0] - g.ns[0], x1 = ci[0] + g.ns[0];
+    const int s0 = g.periodic ? floor_div(x0, g.nb[0]) : 0;
+    const int nseg = g.periodic ? floor_div(x1, g.nb[0]) - s0 + 1 : 1;
+    const int ny = 2 * g.ns[1] + 1;
+    const int total = ny * (2 * g.ns[2] + 1) * nseg;
+    for (int base = 0; base < total; base += G) {
+        int lo = 0, hi = 0, S = 0;   // S: image (x, y, z) as signed bytes
+        const int s = base + sub;
+        if (s < total) {
+            const int row = s / nseg, sx = s0 + (s - row * nseg);
+            int by = ci[1] + row % ny - g.ns[1], bz = ci[2] + row / ny - g.ns[2];
+            int sy = 0, sz = 0;
+            bool in = true;
+            if (g.periodic) {
+                sy = floor_div(by, g.nb[1]); by -= sy * g.nb[1];
+                sz = floor_div(bz, g.nb[2]); bz -= sz * g.nb[2];
+            } else {
+                in = by >= 0 && by < g.nb[1] && bz >= 0 && bz < g.nb[2];
+            }
+            if (in) {
+                const int bx0 = max(x0 - sx * g.nb[0], 0), bx1 = min(x1 - sx * g.nb[0], g.nb[0] - 1);
+                const int br = (bz * g.nb[1] + by) * g.nb[0];
+                lo = 0x7fffffff;
+                for (int bx = bx0; bx <= bx1; ++bx) {
+                    const int k0 = start[br + bx], k1 = end[br + bx];
+                    if (k1 > k0) { lo = min(lo, k0); hi = max(hi, k1); }
+                }
+                S = (sx & 0xFF) | ((sy & 0xFF) << 8) | ((sz & 0xFF) << 16);
+            }
+        }
+        const int live = min(G, total - base);
+        for (int t = 0; t < live; ++t) {
+            const int k0 = __shfl(lo, t, G), k1 = __shfl(hi, t, G);
+            const int sp = __shfl(S, t, G);
+            const int s3[3] = {static_cast<int>(static_cast<int8_t>(sp & 0xFF)),
+                               static_cast<int>(static_cast<int8_t>((sp >> 8) & 0xFF)),
+                               static_cast<int>(static_cast<int8_t>((sp >> 16) & 0xFF))};
+            const bool home = sp == 0;
+            double q[3] = {ri[0], ri[1], ri[2]};
+            if (!home)
+                for (int e = 0; e < 3; ++e)
+                    q[e] = __dsub_rn(ri[e], __dadd_rn(__dadd_rn(__dmul_rn(s3[0], g.a[0 * 3 + e]),
+                                                                __dmul_rn(s3[1], g.a[1 * 3 + e])),
+                                                      __dmul_rn(s3[2], g.a[2 * 3 + e])));
+            for (int kb = k0; kb < k1; kb += G) {
+                const int k = kb + sub;
+                bool hit = false;
+                int j = 0;
+                if (k < k1) {
+                    // explicit roundings: the count and fill passes take the
+                    // same decision for every pair
+                    const double d0 = __dsub_rn(spos[3 * k], q[0]);
+                    const double d1 = __dsub_rn(spos[3 * k + 1], q[1]);
+                    const double d2 = __dsub_rn(spos[3 * k + 2], q[2]);
+                    j = sidx[k];
+                    const double r2 = __dadd_rn(__dadd_rn(__dmul_rn(d0, d0), __dmul_rn(d1, d1)), __dmul_rn(d2, d2));
+                    hit = r2 < g.rl2 && !(home && j == i);
+                }
+                const unsigned m = static_cast<unsigned>(__ballot(hit) >> (lane - sub)) & GM;
+                if (FILL && hit) {
+                    const int at = n + __popc(m & ((1u << sub) - 1u));
+                    if (at >= room) {   // the count pass saw fewer pairs: never write past the row
+                        atomicOr(err, ERR_NEIGH);
+                    } else {
+                        // image in the caller's coordinates: r_ij = pos_j + n a - pos_i
+                        const int n0 = s3[0] - wrap[3 * j] + wi[0];
+                        const int n1 = s3[1] - wrap[3 * j + 1] + wi[1];
+                        const int n2 = s3[2] - wrap[3 * j + 2] + wi[2];
+                        if (n0 < -127 || n0 > 127 || n1 < -127 || n1 > 127 || n2 < -127 || n2 > 127)
+                            atomicOr(err, ERR_NEIGH);   // beyond the signed-byte shift
+                        nbr_j[out + at] = j;
+                        shift[out + at] = (n0 & 0xFF) | ((n1 & 0xFF) << 8) | ((n2 & 0xFF) << 16);
+                    }
+                }
+                n += __popc(m);
+            }
         }
     }
+    if (!FILL && sub == 0) cnt[i] = n;
 }
-
-
 
 // int32 offsets from the 64-bit prefix sum; total[0] = number of pairs.
 __global__ __launch_bounds__(NB_THREADS) void offsets_kernel(int N, const long* __restrict__ off64,
@@ -313,8 +315,9 @@ int pod_build_neighbors(pod_handle* h, int N, const void* pos, const double* cel
     hipLaunchKernelGGL(fill_int_kernel, gbins, tb, 0, h->stream, start, nbins, 0);
     hipLaunchKernelGGL(fill_int_kernel, gbins, tb, 0, h->stream, end, nbins, 0);
     hipLaunchKernelGGL(order_kernel, gb, tb, 0, h->stream, N, key_s, idx_s, wpos, start, end, spos);
-    hipLaunchKernelGGL((search_kernel<false>), gb, tb, 0, h->stream, N, g, key, idx_s, start, end, wpos, spos, wrap,
-                       cnt, nullptr, nullptr, nullptr, h->d_err);
+    const dim3 gs(static_cast<unsigned>((static_cast<long>(N) * NB_LANES + NB_THREADS - 1) / NB_THREADS));
+    hipLaunchKernelGGL((search_kernel<false, NB_LANES>), gs, tb, 0, h->stream, N, g, key, idx_s, start, end, wpos, spos,
+                       wrap, cnt, nullptr, nullptr, nullptr, h->d_err);
     hipLaunchKernelGGL(fill_int_kernel, dim3(1), tb, 0, h->stream, reinterpret_cast<int*>(cnt + N), 2L, 0);
     tbytes = sT;
     if (rocprim::exclusive_scan(tmp, tbytes, cnt, off64, 0L, static_cast<size_t>(N) + 1, rocprim::plus<long>(),
@@ -328,9 +331,8 @@ int pod_build_neighbors(pod_handle* h, int N, const void* pos, const double* cel
     *n_pairs = P;
     if (P > 0x7fffffffL) return POD_ENOTSUP;   // int32 offsets
     if (P > 0 && capacity >= P) {
-        const dim3 gf(static_cast<unsigned>((static_cast<long>(N) + FILL_THREADS - 1) / FILL_THREADS));
-        hipLaunchKernelGGL((search_kernel<true>), gf, dim3(FILL_THREADS), 2 * FILL_CAP * sizeof(int), h->stream, N, g,
-                           key, idx_s, start, end, wpos, spos, wrap, nullptr, offsets, nbr_j, shift, h->d_err);
+        hipLaunchKernelGGL((search_kernel<true, NB_LANES>), gs, tb, 0, h->stream, N, g, key, idx_s, start, end, wpos,
+                           spos, wrap, nullptr, offsets, nbr_j, shift, h->d_err);
         if (hipStreamSynchronize(h->stream) != hipSuccess) return POD_EHIP;
     }
     return hipGetLastError() == hipSuccess ? POD_OK : POD_EHIP;
