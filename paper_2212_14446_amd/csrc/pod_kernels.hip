@@ -136,47 +136,41 @@ __host__ __device__ inline AtomLds atom_lds_layout(int K, int NA, int M, size_t 
     return L;
 }
 
-// dE_i/dr_ij of one pair from the atom's K adjoint rows abr[k * NAP + mu]
-// (eq. (24c)): d/dr [R_k(r) h_k(rhat)] = R'_k h_k rhat + R_k (grad_u h_k -
-// (rhat . grad_u h_k) rhat) / r with h_k = sum_mu Abar_{k mu} A_mu, and
-// rhat . grad_u h = sum_n n h_n over the degree-n parts (Euler).
-
-// The same for any K: one pass over the monomials per radial function.
+// Value and u-gradient of h(u) = sum_mu w_mu A_mu(u) by nested Horner
+// recurrences (x outermost, z innermost; each derivative is carried along
+// with its value): 65 multiply-adds at degree 4 and no table of monomials,
+// where forming the 35 monomials and weighting them takes ~210.
 template <typename T, int PA>
-__device__ __forceinline__ void pair_gradient_any(const T* __restrict__ abr, int K, const T (&A)[n_mono(PA)],
-                                                  const T (&R)[FAST_MAX_K], const T (&dR)[FAST_MAX_K], T ri, T ux,
-                                                  T uy, T uz, T& gx, T& gy, T& gz) {
-    constexpr MonoTable<PA> mt{};
-    constexpr int NA = n_mono(PA);
-    constexpr int NAP = NA;    // rows of one atom are contiguous
-    gx = 0; gy = 0; gz = 0;
+__device__ __forceinline__ void poly_gradient(const T* __restrict__ w, T x, T y, T z, T& h, T& hx, T& hy, T& hz) {
+    hx = T(0); hy = T(0); hz = T(0);
 #pragma unroll
-    for (int k = 0; k < FAST_MAX_K; ++k) {
-        if (k < K) {
-            const T* abk = abr + k * NAP;
-            T hd[PA + 1];
-            T gp[3][PA + 1];
+    for (int a = PA; a >= 0; --a) {
+        const int N = PA - a;          // degree left for y and z
+        T v = T(0), vy = T(0), vz = T(0);
 #pragma unroll
-            for (int n = 0; n <= PA; ++n) { hd[n] = 0; gp[0][n] = 0; gp[1][n] = 0; gp[2][n] = 0; }
+        for (int b = N; b >= 0; --b) {
+            const int n = N - b;       // degree left for z
+            T u = w[mono_index(a, b, n)], uz = T(0);
 #pragma unroll
-            for (int mu = 0; mu < NA; ++mu) {
-                const T w = abk[mu];
-                hd[mt.deg[mu]] += w * A[mu];
-#pragma unroll
-                for (int dd = 0; dd < 3; ++dd)
-                    if (mt.down[mu][dd] >= 0) gp[dd][mt.ex[mu][dd]] += w * A[mt.down[mu][dd]];
+            for (int c = n - 1; c >= 0; --c) {
+                uz = c == n - 1 ? u : uz * z + u;
+                u = u * z + w[mono_index(a, b, c)];
             }
-            T hsum = 0, eul = 0, g0 = 0, g1 = 0, g2 = 0;
-#pragma unroll
-            for (int n = 0; n <= PA; ++n) {
-                hsum += hd[n]; eul += T(n) * hd[n];
-                g0 += T(n) * gp[0][n]; g1 += T(n) * gp[1][n]; g2 += T(n) * gp[2][n];
+            if (b == N) {
+                v = u;
+            } else {
+                vy = b == N - 1 ? v : vy * y + v;
+                vz = b == N - 1 ? uz : vz * y + uz;
+                v = v * y + u;
             }
-            const T a1 = dR[k] * hsum - R[k] * eul * ri;
-            const T a2 = R[k] * ri;
-            gx += a1 * ux + a2 * g0;
-            gy += a1 * uy + a2 * g1;
-            gz += a1 * uz + a2 * g2;
+        }
+        if (a == PA) {
+            h = v;
+        } else {
+            hx = a == PA - 1 ? h : hx * x + h;
+            hy = a == PA - 1 ? vy : hy * x + vy;
+            hz = a == PA - 1 ? vz : hz * x + vz;
+            h = h * x + v;
         }
     }
 }
@@ -656,7 +650,6 @@ struct PArgs {
     double* Facc;            // scatter: FP64 accumulator (3N, zero on entry)
     double* wpart;           // virial partials, column-major [9][nblk]
     int want_W;
-    int gate;                // always 1 (see pair_gradient_blocks)
     int* err;
 };
 
@@ -674,70 +667,6 @@ __host__ __device__ constexpr int pair_acap(int K, int NA, int tsize) {
 __host__ __device__ inline size_t pair_lds_bytes(int K, int NA, size_t tsize) {
     const int t = static_cast<int>(tsize);
     return static_cast<size_t>(pair_acap(K, NA, t)) * abar_stride(K, NA, t) * tsize;
-}
-
-// dE_i/dr_ij of one pair for a radial count KK fixed at compile time
-// (eq. (24c)): W1_mu = sum_k Abar_{k mu} R'_k, W2_mu = sum_k Abar_{k mu} R_k,
-// then g = (sum_mu W1_mu A_mu - sum_n n H_n / r) rhat + (1/r) sum_mu W2_mu
-// grad A_mu with H_n = sum_{deg mu = n} W2_mu A_mu and the gradient sums
-// grouped by the exponent being lowered.
-//
-// Each monomial is contracted in a basic block of its own, entered under
-// `gate`, a kernel argument that is always 1 but unknown to the compiler:
-// with all monomials in one block the code generator issues the K * NA LDS
-// reads of the adjoint rows ahead of the arithmetic and runs out of
-// registers (FP64: 256 VGPRs + 256 AGPRs and scratch, against 180 VGPRs).
-template <typename T, int PA, int KK>
-__device__ __forceinline__ void pair_gradient_blocks(const T* __restrict__ abr, const T (&R)[FAST_MAX_K],
-                                                     const T (&dR)[FAST_MAX_K], T ri, T ux, T uy, T uz, int gate,
-                                                     T& gx, T& gy, T& gz) {
-    constexpr MonoTable<PA> mt{};
-    constexpr int NA = n_mono(PA);
-    constexpr int NAP = NA;    // rows of one atom are contiguous
-    T A[NA];           // monomials, formed in the block that contracts them
-    T s1 = 0, eul = 0, g0 = 0, g1 = 0, g2 = 0;
-    T buf[2][KK];      // the K values of monomial mu in buf[mu & 1]; mu + 1 read ahead
-#pragma unroll
-    for (int k = 0; k < KK; ++k) buf[0][k] = abr[k * NAP];
-#pragma unroll
-    for (int mu = 0; mu < NA; ++mu) {
-        if (gate) {
-            const int cb = mu & 1;
-            if (mu + 1 < NA) {
-#pragma unroll
-                for (int k = 0; k < KK; ++k) buf[cb ^ 1][k] = abr[k * NAP + mu + 1];
-            }
-            if (mu == 0) {
-                A[0] = T(1);
-            } else {
-                const T u = mt.axis[mu] == 0 ? ux : (mt.axis[mu] == 1 ? uy : uz);
-                A[mu] = A[mt.par[mu]] * u;
-            }
-            T w1 = 0, w2 = 0;
-#pragma unroll
-            for (int k = 0; k < KK; ++k) {
-                w1 += buf[cb][k] * dR[k];
-                w2 += buf[cb][k] * R[k];
-            }
-            s1 += w1 * A[mu];
-            // Euler sum n H_n and the gradient sums, each term weighted by its exponent
-            const int dg = mt.deg[mu];
-            if (dg == 1) eul += w2 * A[mu];
-            else if (dg > 1) eul += (T(dg) * w2) * A[mu];
-            T* gd[3] = {&g0, &g1, &g2};
-#pragma unroll
-            for (int dd = 0; dd < 3; ++dd) {
-                if (mt.down[mu][dd] >= 0) {
-                    const int e = mt.ex[mu][dd];
-                    *gd[dd] += (e == 1 ? w2 : T(e) * w2) * A[mt.down[mu][dd]];
-                }
-            }
-        }
-    }
-    const T a1 = s1 - eul * ri;
-    gx = a1 * ux + ri * g0;
-    gy = a1 * uy + ri * g1;
-    gz = a1 * uz + ri * g2;
 }
 
 // Copy nbytes (a multiple of 16) from global memory into LDS with the
@@ -782,23 +711,32 @@ __device__ __forceinline__ void pair_setup(const PArgs<T>& g, bool valid, const 
     q.ux = q.d[0] * q.ri; q.uy = q.d[1] * q.ri; q.uz = q.d[2] * q.ri;
 }
 
+// dE_i/dr_ij of one pair from the atom's K adjoint rows abr[k * NA + mu]
+// (eq. (24c)): d/dr [R_k(r) h_k(rhat)] = R'_k h_k rhat + R_k (grad_u h_k -
+// (rhat . grad_u h_k) rhat) / r with h_k = sum_mu Abar_{k mu} A_mu, so
+// g = (sum_k R'_k h_k - rhat . q / r) rhat + q / r, q = sum_k R_k grad_u h_k.
+// The k loop runs to the model's K, which the compiler does not know: each
+// radial function is a basic block of its own, so that at most one row of
+// LDS reads is in flight and the kernel needs few registers.
 template <typename T, int PA, int KK>
-__device__ __forceinline__ void pair_contract(const PArgs<T>& g, int K, const PairGeom<T>& q, const T* abr, T& gx,
-                                              T& gy, T& gz) {
-    constexpr MonoTable<PA> mt{};
+__device__ __forceinline__ void pair_contract(int K, const PairGeom<T>& q, const T* abr, T& gx, T& gy, T& gz) {
     constexpr int NA = n_mono(PA);
-    if constexpr (KK > 0) {
-        pair_gradient_blocks<T, PA, KK>(abr, q.R, q.dR, q.ri, q.ux, q.uy, q.uz, g.gate, gx, gy, gz);
-    } else {
-        T A[NA];
-        A[0] = T(1);
+    T s = T(0), q0 = T(0), q1 = T(0), q2 = T(0);
 #pragma unroll
-        for (int mu = 1; mu < NA; ++mu) {
-            const T u = mt.axis[mu] == 0 ? q.ux : (mt.axis[mu] == 1 ? q.uy : q.uz);
-            A[mu] = A[mt.par[mu]] * u;
+    for (int k = 0; k < (KK > 0 ? KK : FAST_MAX_K); ++k) {
+        if (k < K) {
+            T h, hx, hy, hz;
+            poly_gradient<T, PA>(abr + k * NA, q.ux, q.uy, q.uz, h, hx, hy, hz);
+            s += q.dR[k] * h;
+            q0 += q.R[k] * hx;
+            q1 += q.R[k] * hy;
+            q2 += q.R[k] * hz;
         }
-        pair_gradient_any<T, PA>(abr, K, A, q.R, q.dR, q.ri, q.ux, q.uy, q.uz, gx, gy, gz);
     }
+    const T a1 = s - (q.ux * q0 + q.uy * q1 + q.uz * q2) * q.ri;
+    gx = a1 * q.ux + q.ri * q0;
+    gy = a1 * q.uy + q.ri * q1;
+    gz = a1 * q.uz + q.ri * q2;
 }
 
 // g_ij of pair p: stored at the pair's own slot and at its reverse slot (the
@@ -835,7 +773,7 @@ template <typename T, int PA, int KK, bool FAST>
 __device__ __forceinline__ void pair_block(const PArgs<T>& g, int blk, T* sAb, double (&vir)[9]) {
     constexpr int NA = n_mono(PA);
     const ParamsT<T>* __restrict__ P = &g.prm;
-    const int K = KK > 0 ? KK : P->K;
+    const int K = P->K;
     const int AST = abar_stride(K, NA, sizeof(T));
     const int acap = pair_acap(K, NA, sizeof(T));
     const int lane = threadIdx.x;
@@ -863,7 +801,7 @@ __device__ __forceinline__ void pair_block(const PArgs<T>& g, int blk, T* sAb, d
     T gx = T(0), gy = T(0), gz = T(0);
     lds_copy_wait();
     if (q.ok && ci >= lo && ci < lo + na0)
-        pair_contract<T, PA, KK>(g, K, q, sAb + static_cast<size_t>(ci - lo) * AST, gx, gy, gz);
+        pair_contract<T, PA, KK>(K, q, sAb + static_cast<size_t>(ci - lo) * AST, gx, gy, gz);
     // further chunks, skipping atoms without pairs in this block
     constexpr int INF = 0x7fffffff;
     const int key = valid ? ci : INF;
@@ -874,7 +812,7 @@ __device__ __forceinline__ void pair_block(const PArgs<T>& g, int blk, T* sAb, d
         lds_copy_issue(g.abar + static_cast<size_t>(base) * AST, sAb, na * AST * static_cast<int>(sizeof(T)), lane);
         lds_copy_wait();
         if (q.ok && ci >= base && ci < base + na)
-            pair_contract<T, PA, KK>(g, K, q, sAb + static_cast<size_t>(ci - base) * AST, gx, gy, gz);
+            pair_contract<T, PA, KK>(K, q, sAb + static_cast<size_t>(ci - base) * AST, gx, gy, gz);
         base = wave_min(key >= base + na ? key : INF);
     }
     if (valid) pair_store<T>(g, p, ci, j, rv, q.ok, gx, gy, gz);
@@ -1336,7 +1274,6 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
     b.Facc = facc;
     b.wpart = reinterpret_cast<double*>(scratch + L.wpart);
     b.want_W = W != nullptr;
-    b.gate = 1;
     b.err = h->d_err;
     if (nblk_p > 0) {
         timing_begin(h, 4);
