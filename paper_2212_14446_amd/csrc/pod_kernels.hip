@@ -17,12 +17,12 @@
 // pair_kernel  (one pair per lane, 64 consecutive list slots per block):
 //   loads the adjoint rows of the block's centre atoms into LDS, re-evaluates
 //   R_k and R'_k and forms dE_i/dr_ij (eq. (24c)); stores it at the pair's
-//   own and reverse slots (gather path, with a reverse-pair index) or adds it
-//   to an FP64 accumulator with device atomics; the virial leaves as
-//   per-block partials.
+//   slot (gather path, with a reverse-pair index) or adds it to an FP64
+//   accumulator with device atomics; the virial leaves as per-block partials.
 // finalize_kernel  sums the partials in a fixed order (E, W, G) and forms the
-//   forces: on the gather path each atom adds what its own list range holds
-//   (32 lanes per atom); otherwise it copies and clears the accumulator.
+//   forces: on the gather path each atom adds its own pairs' gradients and
+//   subtracts their reverses' (32 lanes per atom); otherwise it copies and
+//   clears the accumulator.
 // reverse_kernel  builds the reverse-pair index of a list once.
 // Models beyond these kernels' register budget (angular degree above
 // FAST_MAX_PA or more than FAST_MAX_K radial functions) run the whole
@@ -175,6 +175,19 @@ __device__ __forceinline__ void poly_gradient(const T* __restrict__ w, T x, T y,
     }
 }
 
+// Workgroups are dealt to the eight XCDs of the chip in turn (workgroup i
+// runs on XCD i mod 8).  The blocks of the energy path's kernels are
+// renumbered so that each XCD takes one contiguous range of them:
+// neighbouring blocks read the same positions (per-atom kernel), centre
+// atoms' adjoint rows (pair kernel) and pair gradients (finalize kernel),
+// which are then fetched once into that XCD's L2.
+__device__ __forceinline__ int xcd_block(int i, int n) {
+    constexpr int NX = 8;
+    const int x = i % NX, k = i / NX;
+    const int per = n / NX, rem = n % NX;
+    return x * per + (x < rem ? x : rem) + k;
+}
+
 // One workgroup = one wavefront = APW = 64 / K atoms.  Neighbour slots are
 // processed K at a time per atom ("rounds"); in a round, lane (a, s)
 // evaluates slot s of atom a.
@@ -193,13 +206,14 @@ __device__ __forceinline__ void atom_body(const KArgs<T>& g) {
     const int AST = abar_stride(K, NA, sizeof(T));   // per-atom stride of the adjoint rows
     const int apw = WAVE / K;
     // Mode 2: nw wavefronts per workgroup, wavefront wid taking atom group
-    // grp = blockIdx.x * nw + wid of the ngrp groups of APW atoms (the last
+    // grp = blk * nw + wid of the ngrp groups of APW atoms (the last
     // workgroup may hold groups past the end, which only take part in the
     // workgroup's barriers).  Otherwise one wavefront per workgroup.
     const int nw = MODE == 2 ? static_cast<int>(blockDim.x) / WAVE : 1;
     const int wid = MODE == 2 ? __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / WAVE) : 0;
     const int lane = MODE == 2 ? static_cast<int>(threadIdx.x) % WAVE : static_cast<int>(threadIdx.x);
-    const int grp = MODE == 2 ? static_cast<int>(blockIdx.x) * nw + wid : static_cast<int>(blockIdx.x);
+    const int blk = xcd_block(blockIdx.x, gridDim.x);
+    const int grp = MODE == 2 ? blk * nw + wid : blk;
     const int ngrp = MODE == 2 ? (g.N + apw - 1) / apw : static_cast<int>(gridDim.x);
     const bool grp_live = MODE != 2 || grp < ngrp;
     const int al = lane / K;
@@ -627,9 +641,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void
 // with their derivatives and contracts the monomials of its pair with the K
 // rows of its centre atom.
 //
-// Outputs: on the gather path g is stored at the pair's own slot p and at
-// its reverse slot rev(p), and the finalize kernel forms each atom's force
-// from its own list range in a fixed order; without a reverse index, g is
+// Outputs: on the gather path g is stored at the pair's slot p, and the
+// finalize kernel forms each atom's force from its own pairs and their
+// reverses in a fixed order; without a reverse index, g is
 // added to an FP64 accumulator with atomics.  The virial leaves as one
 // partial per block.
 template <typename T>
@@ -641,12 +655,10 @@ struct PArgs {
     const int* offsets;
     const int* nbr_j;
     const int* shift;
-    const int* rev;          // reverse-pair index (gather path) or null
     const T* abar;           // adjoint rows [N][K][NA]
     const int* centre;       // centre atom of every pair (written by the atom kernel)
     const T* pdv;            // pair vectors r_ij, zero for a listed pair that is not a neighbour (same)
-    T* gbuf;                 // gather: g_ij stored at slot rev(p) (3P)
-    T* gown;                 // gather: g_ij stored at slot p (3P)
+    T* gown;                 // gather: g_ij of pair p (3P)
     double* Facc;            // scatter: FP64 accumulator (3N, zero on entry)
     double* wpart;           // virial partials, column-major [9][nblk]
     int want_W;
@@ -739,21 +751,14 @@ __device__ __forceinline__ void pair_contract(int K, const PairGeom<T>& q, const
     gz = a1 * q.uz + q.ri * q2;
 }
 
-// g_ij of pair p: stored at the pair's own slot and at its reverse slot (the
-// finalize kernel gathers F_n = sum over n's slots of own - reverse), or
-// added to both atoms with atomics.
+// g_ij of pair p: stored at the pair's slot (the finalize kernel gathers
+// F_n = sum over n's slots of g_p - g_rev(p)), or added to both atoms with
+// atomics.
 template <typename T>
-__device__ __forceinline__ void pair_store(const PArgs<T>& g, int p, int ci, int j, int rv, bool ok, T gx, T gy,
-                                           T gz) {
-    if (g.gbuf) {
+__device__ __forceinline__ void pair_store(const PArgs<T>& g, int p, int ci, int j, bool ok, T gx, T gy, T gz) {
+    if (g.gown) {
         T* go = g.gown + 3 * static_cast<size_t>(p);
         go[0] = gx; go[1] = gy; go[2] = gz;
-        if (rv >= 0 && rv < g.P) {
-            T* gp3 = g.gbuf + 3 * static_cast<size_t>(rv);
-            gp3[0] = gx; gp3[1] = gy; gp3[2] = gz;
-        } else {
-            atomicOr(g.err, ERR_NEIGH);
-        }
     } else if (ok) {
         atomicAdd(&g.Facc[3 * j + 0], -static_cast<double>(gx));
         atomicAdd(&g.Facc[3 * j + 1], -static_cast<double>(gy));
@@ -779,22 +784,21 @@ __device__ __forceinline__ void pair_block(const PArgs<T>& g, int blk, T* sAb, d
     const int lane = threadIdx.x;
     const int p = blk * WAVE + lane;
     const bool valid = p < g.P;
-    // everything the pair needs, requested at once: centre atom, pair vector,
-    // reverse slot (gather path) or neighbour index (atomic path)
+    // everything the pair needs, requested at once: centre atom, pair vector
+    // and, on the atomic path, neighbour index
     // (issued on every lane: a lane past the end reads the last pair)
     const int pc = valid ? p : g.P - 1;
-    int ci = g.centre[pc], rv = -1, j = -1;
+    int ci = g.centre[pc], j = -1;
     T dv[3] = {g.pdv[3 * static_cast<size_t>(pc) + 0], g.pdv[3 * static_cast<size_t>(pc) + 1],
                g.pdv[3 * static_cast<size_t>(pc) + 2]};
-    if (g.gbuf) rv = g.rev[pc];
-    else j = g.nbr_j[pc];
+    if (!g.gown) j = g.nbr_j[pc];
     int lo = g.centre[blk * WAVE];
     lo = lo < 0 ? 0 : (lo > g.N - 1 ? g.N - 1 : lo);
     const int na0 = (g.N - lo < acap) ? g.N - lo : acap;
     wave_sync();   // rows of a previous block are no longer read
     lds_copy_issue(g.abar + static_cast<size_t>(lo) * AST, sAb, na0 * AST * static_cast<int>(sizeof(T)), lane);
     ci = ci < 0 ? 0 : (ci > g.N - 1 ? g.N - 1 : ci);
-    if (!g.gbuf && (j < 0 || j >= g.N)) j = ci;   // malformed list: reported by the atom kernel
+    if (!g.gown && (j < 0 || j >= g.N)) j = ci;   // malformed list: reported by the atom kernel
 
     PairGeom<T> q;
     pair_setup<T, KK, FAST>(g, valid, dv, q);
@@ -815,7 +819,7 @@ __device__ __forceinline__ void pair_block(const PArgs<T>& g, int blk, T* sAb, d
             pair_contract<T, PA, KK>(K, q, sAb + static_cast<size_t>(ci - base) * AST, gx, gy, gz);
         base = wave_min(key >= base + na ? key : INF);
     }
-    if (valid) pair_store<T>(g, p, ci, j, rv, q.ok, gx, gy, gz);
+    if (valid) pair_store<T>(g, p, ci, j, q.ok, gx, gy, gz);
     if (q.ok) {
         const double dd[3] = {double(q.d[0]), double(q.d[1]), double(q.d[2])};
         const double gg[3] = {double(gx), double(gy), double(gz)};
@@ -824,17 +828,6 @@ __device__ __forceinline__ void pair_block(const PArgs<T>& g, int blk, T* sAb, d
 #pragma unroll
             for (int y = 0; y < 3; ++y) vir[3 * x + y] -= dd[x] * gg[y];
     }
-}
-
-// Workgroups are dealt to the eight XCDs of the chip in turn (workgroup i
-// runs on XCD i mod 8).  The pair blocks are renumbered so that each XCD
-// takes one contiguous range of them: neighbouring blocks share centre
-// atoms, whose adjoint rows are then fetched once into that XCD's L2.
-__device__ __forceinline__ int xcd_block(int i, int n) {
-    constexpr int NX = 8;
-    const int x = i % NX, k = i / NX;
-    const int per = n / NX, rem = n % NX;
-    return x * per + (x < rem ? x : rem) + k;
 }
 
 // KK: the radial count when fixed at compile time (4 or 6), 0 for any K.
@@ -866,10 +859,11 @@ __global__ __launch_bounds__(64) void pair_kernel(PArgs<T> g) {
 // Totals and forces.  Blocks 0 .. 9 + M: column sums of the block partials
 // in a fixed order (column 0 -> E and 10.. -> G from the atom kernel's
 // blocks, 1..9 -> W from the pair kernel's blocks).  Remaining blocks, with
-// a reverse index: F_n = sum over the slots p of n of gown[p] - gbuf[p],
-// where gown[p] holds g of pair p and gbuf[p] g of its reverse (8 atoms x 32
-// lanes per block, deterministic); without one: F = Facc (accumulated with
-// atomics) and Facc cleared for the next call.
+// a reverse index: F_n = sum over the slots p of n of g_p - g_rev(p) (8 atoms
+// x 32 lanes per block, deterministic); without one: F = Facc (accumulated
+// with atomics) and Facc cleared for the next call.  Reading the reverse
+// pair's gradient here costs a gather of 12 or 24 bytes; storing every
+// gradient at its reverse slot as well cost scattered partial-line writes.
 template <typename T>
 struct FinArgs {
     const double* part;    // atom-kernel partials [10 + M][nblk]
@@ -882,8 +876,7 @@ struct FinArgs {
     double* Facc;
     T* F;
     long n3;
-    const T* gbuf;         // gather path: g stored at reverse slots
-    const T* gown;         // gather path: g stored at own slots
+    const T* gown;         // gather path: g of every pair
     const int* rev;
     const int* offsets;
     int N, P;
@@ -894,7 +887,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void finalize_kernel(FinArgs<T> f) {
     const int col = blockIdx.x;
     if (col >= f.ncol) {
-        const int fb = col - f.ncol;
+        const int fb = xcd_block(col - f.ncol, static_cast<int>(gridDim.x) - f.ncol);
         if (f.rev) {
             const int a = fb * 8 + static_cast<int>(threadIdx.x) / 32;
             const int s0 = threadIdx.x % 32;
@@ -902,12 +895,17 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs<T> f) {
             if (a < f.N) {
                 const int b = f.offsets[a], e = f.offsets[a + 1];
                 if (b >= 0 && e >= b && e <= f.P) {
-                    // slot p of atom a: g of pair p (a -> j) and g of its reverse (j -> a)
+                    // g of pair p (a -> j) and g of its reverse (j -> a)
                     for (int p = b + s0; p < e; p += 32) {
-                        const size_t o = 3 * static_cast<size_t>(p);
-                        f0 += static_cast<double>(f.gown[o + 0]) - static_cast<double>(f.gbuf[o + 0]);
-                        f1 += static_cast<double>(f.gown[o + 1]) - static_cast<double>(f.gbuf[o + 1]);
-                        f2 += static_cast<double>(f.gown[o + 2]) - static_cast<double>(f.gbuf[o + 2]);
+                        const int rv = f.rev[p];
+                        if (rv < 0 || rv >= f.P) {
+                            atomicOr(f.err, ERR_NEIGH);
+                            continue;
+                        }
+                        const size_t o = 3 * static_cast<size_t>(p), v = 3 * static_cast<size_t>(rv);
+                        f0 += static_cast<double>(f.gown[o + 0]) - static_cast<double>(f.gown[v + 0]);
+                        f1 += static_cast<double>(f.gown[o + 1]) - static_cast<double>(f.gown[v + 1]);
+                        f2 += static_cast<double>(f.gown[o + 2]) - static_cast<double>(f.gown[v + 2]);
                     }
                 }
             }
@@ -1126,7 +1124,7 @@ WideArgs<T> wide_args(const KArgs<T>& a) {
     w.pos = a.pos; w.offsets = a.offsets; w.nbr_j = a.nbr_j; w.shift = a.shift;
     w.coef = a.coef; w.D = a.D; w.E_atom = a.E_atom;
     w.part = a.part; w.wpart = nullptr;
-    w.gown = nullptr; w.gbuf = nullptr; w.rev = nullptr; w.Facc = nullptr;
+    w.gown = nullptr; w.Facc = nullptr;
     w.rec = nullptr; w.rs = 0;
     w.want_G = a.want_G; w.want_back = a.want_back; w.want_W = 0;
     w.err = a.err;
@@ -1165,11 +1163,11 @@ int descriptors_impl(pod_handle* h, int N, int P, const void* pos, const double*
 // aligned pieces): atom-kernel partials [10 + M][nblk], pair-kernel virial
 // partials [9][nblk_p], adjoint rows [N][K][NA] (per-atom stride padded to
 // 16 bytes), centre atom and pair vector of each pair, on the gather path
-// the pair gradients [P][3] at reverse and at own slots, and for the
+// the pair gradients [P][3], and for the
 // wide-degree kernel (no adjoint rows, centres or pair vectors) the pair
 // records [P][4 + 2K].
 struct EfScratch {
-    size_t part, wpart, abar, centre, pdv, gbuf, gown, rec, total;
+    size_t part, wpart, abar, centre, pdv, gown, rec, total;
 };
 
 EfScratch ef_scratch_layout(int N, int P, int K, int PA, int M, size_t tsize, bool back, bool gather) {
@@ -1186,7 +1184,6 @@ EfScratch ef_scratch_layout(int N, int P, int K, int PA, int M, size_t tsize, bo
     o += (back && !wide) ? al(static_cast<size_t>(N) * abar_stride(K, n_mono(PA), static_cast<int>(tsize)) * tsize) : 0;
     L.centre = o; o += wide ? 0 : al((static_cast<size_t>(P) + 1) * sizeof(int));   // entry P: spare for empty slots
     L.pdv = o; o += wide ? 0 : al((static_cast<size_t>(P) + 1) * 3 * tsize);
-    L.gbuf = o; o += gather ? al(static_cast<size_t>(P > 0 ? P : 1) * 3 * tsize) : 0;
     L.gown = o; o += gather ? al(static_cast<size_t>(P > 0 ? P : 1) * 3 * tsize) : 0;
     L.rec = o; o += wide ? al(static_cast<size_t>(P > 0 ? P : 1) * wide_rec_stride(K, true) * tsize) : 0;
     L.total = o;
@@ -1225,9 +1222,7 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
         WideArgs<T> w = wide_args(a);
         const int nblk_w = wide_blocks(N);
         w.wpart = reinterpret_cast<double*>(scratch + L.wpart);
-        w.gbuf = gather ? reinterpret_cast<T*>(scratch + L.gbuf) : nullptr;
         w.gown = gather ? reinterpret_cast<T*>(scratch + L.gown) : nullptr;
-        w.rev = gather ? rev : nullptr;
         w.Facc = (back && !gather) ? facc : nullptr;
         w.rec = reinterpret_cast<T*>(scratch + L.rec);
         w.rs = wide_rec_stride(h->K, true);
@@ -1243,7 +1238,7 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
         fa.E = E; fa.W = back ? W : nullptr; fa.G = G;
         fa.Facc = facc; fa.F = static_cast<T*>(F);
         fa.n3 = (back && !gather) ? 3L * N : 0L;
-        fa.gbuf = w.gbuf; fa.gown = w.gown; fa.rev = gather ? rev : nullptr; fa.offsets = offsets;
+        fa.gown = w.gown; fa.rev = gather ? rev : nullptr; fa.offsets = offsets;
         fa.N = N; fa.P = P; fa.err = h->d_err;
         const int nfb = gather ? (N + 7) / 8 : static_cast<int>((fa.n3 + 255) / 256);
         if (E || W || G || nfb > 0) {
@@ -1267,9 +1262,7 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
     PArgs<T> b;
     b.prm = a.prm; b.N = N; b.P = P; b.pos = a.pos; b.cell = a.cell;
     b.offsets = offsets; b.nbr_j = nbr_j; b.shift = shift;
-    b.rev = gather ? rev : nullptr;
     b.abar = a.abar; b.centre = a.centre; b.pdv = a.pdv;
-    b.gbuf = gather ? reinterpret_cast<T*>(scratch + L.gbuf) : nullptr;
     b.gown = gather ? reinterpret_cast<T*>(scratch + L.gown) : nullptr;
     b.Facc = facc;
     b.wpart = reinterpret_cast<double*>(scratch + L.wpart);
@@ -1291,7 +1284,7 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
     fa.E = E; fa.W = back ? W : nullptr; fa.G = G;
     fa.Facc = facc; fa.F = static_cast<T*>(F);
     fa.n3 = (back && !gather) ? 3L * N : 0L;
-    fa.gbuf = b.gbuf; fa.gown = b.gown; fa.rev = gather ? rev : nullptr; fa.offsets = offsets;
+    fa.gown = b.gown; fa.rev = gather ? rev : nullptr; fa.offsets = offsets;
     fa.N = N; fa.P = P; fa.err = h->d_err;
     const int nfb = gather ? (N + 7) / 8 : static_cast<int>((fa.n3 + 255) / 256);
     if (E || W || G || nfb > 0) {

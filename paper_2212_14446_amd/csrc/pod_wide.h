@@ -31,9 +31,7 @@ struct WideArgs {
     T* E_atom;           // per-atom energy or null (mode 1)
     double* part;        // block partials [10 + M][nblk]: column 0 E, 10.. G (mode 1)
     double* wpart;       // block virial partials [9][nblk]
-    T* gown;             // gather path: g of pair p at slot p
-    T* gbuf;             // gather path: g of pair p at slot rev[p]
-    const int* rev;
+    T* gown;             // gather path: g of every pair
     double* Facc;        // atomic path: FP64 force accumulator (zero on entry)
     T* rec;              // pair records, P x rs (scratch)
     int rs;              // record stride: 4 + K, or 4 + 2 K with R'_k (mode 1)

@@ -23,7 +23,7 @@
 //      g_ij = sum_{k n} Abar_{k n} [R'_k A_n rhat + R_k (grad A_n - |n| A_n
 //      rhat) / r] (Euler identity for the homogeneous A_n), summed over the
 //      eight lanes by shuffles in a fixed order, then stored at the pair's
-//      own and reverse slots (or added to the force accumulator).
+//      slot (or added to the force accumulator).
 // E, G and the virial leave as per-workgroup partials that the energy path's
 // finalize kernel sums in a fixed order.  Evaluating the radial functions in
 // a kernel of their own keeps their constants and temporaries out of the
@@ -480,16 +480,9 @@ __global__ __launch_bounds__(WT) void wide_kernel(WideArgs<T> g) {
                 const T gy = ok ? sa * u[1] + ri * gv1 : T(0);
                 const T gz = ok ? sa * u[2] + ri * gv2 : T(0);
                 if (s == 0 && in) {
-                    if (g.gbuf) {
+                    if (g.gown) {
                         T* go = g.gown + 3 * static_cast<size_t>(p);
                         go[0] = gx; go[1] = gy; go[2] = gz;
-                        const int rv = g.rev[p];
-                        if (rv >= 0 && rv < g.P) {
-                            T* gp3 = g.gbuf + 3 * static_cast<size_t>(rv);
-                            gp3[0] = gx; gp3[1] = gy; gp3[2] = gz;
-                        } else {
-                            eb |= ERR_NEIGH;
-                        }
                     } else if (ok && g.Facc) {
                         const int j = g.nbr_j[p];
                         atomicAdd(&g.Facc[3 * j + 0], -static_cast<double>(gx));
