@@ -200,7 +200,7 @@ int pod_energy_forces_noalloc(pod_handle* h, int N, int P, const void* pos, cons
                               const void* c, void* E_atom, double* E, void* F, double* W, double* G);
 
 /* Batched descriptor-matrix assembly for fitting (Sec. IV.A, eqs. (58a),
- * (63a)): many independent periodic cells in one persistent launch, FP64
+ * (63a)): many independent periodic cells in one call, FP64
  * handles only (POD_ENOTSUP otherwise).
  *   n_cfg        : number of cells; N, P: total atoms and pairs over all cells
  *   cfg_atom_off : n_cfg + 1 ints (device); cell c owns atoms
@@ -221,16 +221,17 @@ int pod_energy_forces_noalloc(pod_handle* h, int N, int P, const void* pos, cons
  *   tune         : launch shape (see pod_tune) or NULL for the defaults.
  * The library plans on the host from offsets and cfg_atom_off (a blocking
  * device-to-host copy of both), so the call returns after the plan, with the
- * kernel queued on the handle's stream.  A cell with more atoms than the
+ * kernels queued on the handle's stream.  A cell with more atoms than the
  * LDS accumulator holds (the limit depends on M and the tune) gives
  * POD_ENOTSUP.  Scratch grows in the handle (POD_ENOMEM on failure). */
 typedef struct pod_tune {
-    int cw;       /* descriptor columns per dG/dR chunk (0 = default 17; lowered
-                     until the cell's LDS accumulator fits the device's LDS
-                     per workgroup) */
-    int nblocks;  /* persistent workgroups (0 = default 512, capped at n_cfg) */
-    int threads;  /* threads per workgroup, a multiple of 64 up to 512
-                     (0 = default 512; otherwise POD_EINVAL) */
+    int cw;       /* most descriptor columns per dG/dR chunk (0 = library's
+                     choice; lowered until the cell's LDS accumulator fits the
+                     device's LDS per workgroup) */
+    int nblocks;  /* persistent dG/dR workgroups (0 = one per cell, radial index
+                     and chunk) */
+    int threads;  /* threads per dG/dR workgroup, a multiple of 64 up to 512
+                     (0 = library's choice; otherwise POD_EINVAL) */
 } pod_tune;
 
 int pod_batch_assemble(pod_handle* h, int n_cfg, int N, int P, const int* cfg_atom_off,

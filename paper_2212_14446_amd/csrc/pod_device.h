@@ -391,5 +391,44 @@ __device__ __forceinline__ void accumulate_basis(T (&acc)[n_mono(PA)], T Rm, T u
     }
 }
 
+// Value and u-gradient of h(u) = sum_mu w_mu A_mu(u) by nested Horner
+// recurrences (x outermost, z innermost; each derivative is carried along
+// with its value): 65 multiply-adds at degree 4 and no table of monomials,
+// where forming the 35 monomials and weighting them takes ~210.
+template <typename T, int PA>
+__device__ __forceinline__ void poly_gradient(const T* __restrict__ w, T x, T y, T z, T& h, T& hx, T& hy, T& hz) {
+    hx = T(0); hy = T(0); hz = T(0);
+#pragma unroll
+    for (int a = PA; a >= 0; --a) {
+        const int N = PA - a;          // degree left for y and z
+        T v = T(0), vy = T(0), vz = T(0);
+#pragma unroll
+        for (int b = N; b >= 0; --b) {
+            const int n = N - b;       // degree left for z
+            T u = w[mono_index(a, b, n)], uz = T(0);
+#pragma unroll
+            for (int c = n - 1; c >= 0; --c) {
+                uz = c == n - 1 ? u : uz * z + u;
+                u = u * z + w[mono_index(a, b, c)];
+            }
+            if (b == N) {
+                v = u;
+            } else {
+                vy = b == N - 1 ? v : vy * y + v;
+                vz = b == N - 1 ? uz : vz * y + uz;
+                v = v * y + u;
+            }
+        }
+        if (a == PA) {
+            h = v;
+        } else {
+            hx = a == PA - 1 ? h : hx * x + h;
+            hy = a == PA - 1 ? vy : hy * x + vy;
+            hz = a == PA - 1 ? vz : hz * x + vz;
+            h = h * x + v;
+        }
+    }
+}
+
 }  // namespace dev
 }  // namespace pod
