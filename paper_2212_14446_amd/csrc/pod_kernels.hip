@@ -812,8 +812,12 @@ __device__ __forceinline__ void pair_body(const PArgs<T>& g) {
     }
 }
 
+// FP32 up to degree 4 is held to seven wavefronts per SIMD (72 registers).
+constexpr int pair_waves(int tsize, int PA) { return tsize == 4 && PA <= 4 ? 7 : 1; }
+
 template <typename T, int PA, int KK, bool FAST>
-__global__ __launch_bounds__(64) void pair_kernel(PArgs<T> g) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(pair_waves(sizeof(T), PA)))) void pair_kernel(
+    PArgs<T> g) {
     pair_body<T, PA, KK, FAST>(g);
 }
 
