@@ -16,6 +16,7 @@ namespace pod {
 constexpr int WIDE_THREADS = 256;
 constexpr int WIDE_CHUNK = 32;          // pairs staged per step
 constexpr int WIDE_MAX_BLOCKS = 2048;   // persistent workgroups
+constexpr int WIDE_PARTS = 48;          // parts of a radial index's degree sums, at most
 
 template <typename T>
 struct WideArgs {
@@ -40,17 +41,26 @@ struct WideArgs {
 };
 
 // LDS layout of one wide_kernel workgroup, in bytes: the energy coefficients
-// (M), the monomial codes (NA ints), with 4-body terms the packed eq. (30a)
-// tables (wide_tab_ints ints), the basis rows [K][NA] (later the adjoint
-// rows), the degree sums [K][PA + 1], the staged R_k and R'_k
-// [2][WIDE_CHUNK][POD_MAX_K], unit vectors and distances [WIDE_CHUNK][4],
-// the powers of the unit vectors' components [WIDE_CHUNK][3][PA + 1], and a
-// reduction area.
+// (M), the monomial codes (NA ints) and factorials, 1 / a, with 4-body terms the
+// packed eq. (30a) tables (wide_tab_ints ints), the basis rows [K][row stride]
+// (later the adjoint rows), the degree sums [K][PA + 1] and their parts
+// [K][WIDE_PARTS], B_{k 0} (K), the pair records of a chunk [WIDE_CHUNK][4 +
+// 2K], the divided powers of the unit vectors' components
+// [WIDE_CHUNK][3][PA + 2], the wavefronts' gradient sums [4][WIDE_CHUNK][4],
+// and a reduction area.
 struct WideLds {
-    size_t coef, code, tab, b, s, r, u, pw, red, total;
+    size_t coef, code, fact, inv, tab, b, s, part, b0, r, pw, g, red, total;
 };
 
 __host__ __device__ constexpr size_t wide_align(size_t b) { return (b + 15) & ~size_t(15); }
+
+// Row stride of the basis and adjoint rows: 16 modulo 32, so that two rows'
+// runs of 16 doubles (the operand of a matrix instruction) fall into
+// different LDS banks.
+__host__ __device__ constexpr int wide_row(int NA) { return (NA + 15) / 32 * 32 + 16; }
+// Stride of a pair's power table: three components with a leading zero
+// (u^-1), made odd.
+__host__ __device__ constexpr int wide_pw(int PA) { return (3 * (PA + 2)) | 1; }
 
 // ints of the packed 4-body tables: per index p its triple and term range
 // (3 KA4), the terms (NT4), the occurrence ranges (NA4 + 1), the
@@ -65,13 +75,17 @@ __host__ __device__ constexpr WideLds wide_lds(int K, int PA, int M, bool four, 
     WideLds L{};
     L.coef = 0;
     L.code = wide_align(L.coef + static_cast<size_t>(M) * ts);
-    L.tab = wide_align(L.code + NA * sizeof(int));
+    L.fact = wide_align(L.code + NA * sizeof(int));
+    L.inv = wide_align(L.fact + NA * sizeof(float));
+    L.tab = wide_align(L.inv + (POD_MAX_P + 1) * ts);
     L.b = wide_align(L.tab + (four ? static_cast<size_t>(wide_tab_ints()) * sizeof(int) : 0));
-    L.s = wide_align(L.b + static_cast<size_t>(K) * NA * ts);
-    L.r = wide_align(L.s + static_cast<size_t>(K) * (PA + 1) * ts);
-    L.u = wide_align(L.r + 2 * static_cast<size_t>(WIDE_CHUNK) * POD_MAX_K * ts);
-    L.pw = wide_align(L.u + 4 * static_cast<size_t>(WIDE_CHUNK) * ts);
-    L.red = wide_align(L.pw + static_cast<size_t>(WIDE_CHUNK) * 3 * (PA + 1) * ts);
+    L.s = wide_align(L.b + static_cast<size_t>(K) * wide_row(static_cast<int>(NA)) * ts);
+    L.part = wide_align(L.s + static_cast<size_t>(K) * (PA + 1) * ts);
+    L.b0 = wide_align(L.part + static_cast<size_t>(K) * WIDE_PARTS * ts);
+    L.r = wide_align(L.b0 + static_cast<size_t>(K) * ts);
+    L.pw = wide_align(L.r + static_cast<size_t>(WIDE_CHUNK) * (4 + 2 * K) * ts);
+    L.g = wide_align(L.pw + static_cast<size_t>(WIDE_CHUNK) * wide_pw(PA) * ts);
+    L.red = wide_align(L.g + 4 * static_cast<size_t>(WIDE_CHUNK) * 4 * ts);
     L.total = wide_align(L.red + 16 * sizeof(double));
     return L;
 }

@@ -7,10 +7,12 @@
 //   and rhat = 0 for a listed pair beyond the cut-off.
 // wide_kernel: one 256-thread workgroup serves one atom at a time
 //   (persistent over the atoms i = blk, blk + nblk, ...):
-//   1. basis (eq. (24b)): the records of WIDE_CHUNK pairs and the powers of
-//      their unit vectors' components are staged in LDS, and thread t
-//      accumulates B_{k n} for its monomials n = t, t + 256 and every k in
-//      registers; the rows then go to LDS;
+//   1. basis (eq. (24b)) as a matrix product over the pairs on the matrix
+//      cores, B_{k n} = sum_p R_k(p) A_n(p): the records of WIDE_CHUNK pairs and
+//      the powers of their unit vectors' components are staged in LDS;
+//      wavefront w takes the 16-monomial tiles w, w + 4, .. (16 radial rows, 4
+//      pairs per instruction) and forms A_n from three powers; the rows then
+//      go to LDS;
 //   2. contraction: degree sums S_{k a} = sum_{|n| = a} c_n B_{k n}^2,
 //      thread d forms descriptor d: D2 = B_{k 0} (eq. (25)), D3 = S
 //      (eq. (26a)), D4 by eq. (27a) for (a, 0, 0) and by the merged terms of
@@ -19,11 +21,20 @@
 //      4-body part gathered per monomial from a table of its occurrences in
 //      the eq. (30a) terms (fixed order, no atomics); row k overwrites basis
 //      row k in LDS;
-//   4. pair gradients (eq. (24c)): eight lanes per pair split the monomials,
-//      g_ij = sum_{k n} Abar_{k n} [R'_k A_n rhat + R_k (grad A_n - |n| A_n
-//      rhat) / r] (Euler identity for the homogeneous A_n), summed over the
-//      eight lanes by shuffles in a fixed order, then stored at the pair's
-//      slot (or added to the force accumulator).
+//   4. pair gradients (eq. (24c)): W'_n = sum_k Abar_{k n} R'_k and W_n = sum_k
+//      Abar_{k n} R_k of 16 monomials and 16 pairs at a time on the matrix
+//      cores; the lane that holds W', W of (n, p) adds W'_n A_n and W_n grad
+//      A_n; g_ij = (sum W' A - rhat . q / r) rhat + q / r with q = sum W grad A
+//      (Euler identity for the homogeneous A_n).  The sums over a pair's lanes
+//      and wavefronts have a fixed order; g is stored at the pair's slot (or
+//      added to the force accumulator).
+// With divided powers u^a / a! the gradient of a monomial is another product of
+// the same table (d/du lowers a); the basis rows are multiplied, and the
+// adjoint rows pre-multiplied, by a! b! c!.
+// Vector form of 1 and 4 (one monomial per thread with 12 radial values from
+// LDS per pair; eight lanes per pair with K adjoint values from LDS per
+// monomial), 15,840 atoms, K = 12, P3 = 10, FP64: WIDE_BEFORE us; the operands
+// now stay in registers: WIDE_AFTER us.
 // E, G and the virial leave as per-workgroup partials that the energy path's
 // finalize kernel sums in a fixed order.  Evaluating the radial functions in
 // a kernel of their own keeps their constants and temporaries out of the
@@ -46,9 +57,11 @@ using namespace dev;
 
 constexpr int WT = WIDE_THREADS;
 constexpr int CH = WIDE_CHUNK;
-constexpr int GSUB = WT / CH;                               // lanes per pair in the gradient pass
+constexpr int NWV = WT / WAVE;
 constexpr int NA_MAX = n_mono(POD_MAX_P);                   // 286
-constexpr int MPT = (NA_MAX + WT - 1) / WT;                 // monomials per thread in the basis pass
+constexpr int MPT = (NA_MAX + WT - 1) / WT;                 // monomials per thread in the adjoint
+constexpr int TPW = ((NA_MAX + 15) / 16 + NWV - 1) / NWV;   // 16-monomial tiles per wavefront
+constexpr int KSTEP = (POD_MAX_K + 3) / 4;                  // matrix steps over the radial index
 constexpr int DPT = 2;                                      // descriptor columns per thread
 constexpr int NA4 = n_mono(POD_MAX_P4);                     // monomials that enter eq. (30a)
 constexpr int KA4 = n_partitions(POD_MAX_P4);               // 23
@@ -56,7 +69,7 @@ constexpr int NT4 = D4Table<POD_MAX_P4>::NT;                // merged eq. (30a) 
 
 static_assert(1 + POD_MAX_K + POD_MAX_K * (POD_MAX_P + 1) + POD_MAX_K * KA4 <= DPT * WT,
               "descriptor columns per thread");
-static_assert(GSUB == 8, "the gradient reduction assumes eight lanes per pair");
+static_assert(CH % 16 == 0 && POD_MAX_K <= 16 && NWV == 4, "tiles of the matrix products");
 
 // Monomial codes: a | b << 4 | c << 8 | degree << 12 | multinomial << 16
 // (device order of pod_tables.h).  Packed eq. (30a) tables for 4-body indices
@@ -118,6 +131,54 @@ __device__ const WideTables kWide = make_wide_tables();
 // 4-body index of the triple (a, 0, 0): the first triple of degree a.
 __device__ __forceinline__ int p_a00(const int* tab, int a) { return tab[T_PA00 + a]; }
 
+// 16 x 16 x 4 matrix instruction of the working precision: operands A[i][k] and
+// B[k][j] in lane 16 k + i (j); element e of lane 16 g + j is row row(g, e),
+// column j of the result.
+template <typename T> struct Mx;
+template <> struct Mx<double> {
+    typedef double vec __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ vec mul(double a, double b, vec c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int g, int e) { return g + 4 * e; }
+};
+template <> struct Mx<float> {
+    typedef float vec __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ vec mul(float a, float b, vec c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int g, int e) { return 4 * g + e; }
+};
+
+// Divided powers u^a / a!, a = 0 .. PA, behind a leading zero (inv[a] = 1 / a).
+template <typename T>
+__device__ __forceinline__ void divided_powers(T* pw, T u, int PA, const T* inv) {
+    pw[0] = T(0);
+    T v = T(1);
+    pw[1] = v;
+    for (int a = 1; a <= PA; ++a) {
+        v *= u * inv[a];
+        pw[a + 1] = v;
+    }
+}
+
+// Parts of the degree sums S_a = sum_{|n| = a} c_n B_n^2: runs of at most
+// PART_LEN monomials of one degree, so that no thread adds a long run alone.
+constexpr int PART_LEN = 8;
+constexpr int part_begin(int a) {      // parts of the degrees below a
+    int p = 0;
+    for (int d = 0; d < a; ++d) p += (n_of_degree(d) + PART_LEN - 1) / PART_LEN;
+    return p;
+}
+struct PartTable {
+    int begin[POD_MAX_P + 2];
+    constexpr PartTable() : begin{} {
+        for (int a = 0; a < POD_MAX_P + 2; ++a) begin[a] = part_begin(a);
+    }
+};
+__device__ const PartTable kParts = PartTable();
+static_assert(part_begin(POD_MAX_P + 1) <= WIDE_PARTS, "parts of the degree sums");
+
 // Sum over the workgroup in a fixed order (shuffles within each wavefront,
 // then the four wavefront sums in order); every thread gets the result.
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -175,13 +236,19 @@ __global__ __launch_bounds__(WT) void wide_pair_kernel(WideArgs<T> g) {
     if ((tid & 63) == 0 && eb) atomicOr(g.err, eb);
 }
 
+// Wavefronts per SIMD: the LDS allows three workgroups of the energy kernel per
+// compute unit.
+constexpr int wide_waves(int mode) { return mode == 0 ? 4 : 2; }
+
 template <typename T, int MODE>
-__global__ __launch_bounds__(WT) void wide_kernel(WideArgs<T> g) {
+__global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(wide_waves(MODE)))) void wide_kernel(WideArgs<T> g) {
     extern __shared__ __align__(16) unsigned char smem[];
     const ParamsT<T>& prm = g.prm;
     const int K = prm.K, PA = prm.PA, M = prm.M;
     const int NA = n_mono(PA);
-    const int PA1 = PA + 1;
+    const int NR = wide_row(NA);       // row stride of the basis rows
+    const int PA1 = PA + 1, PA2 = PA + 2, PST = wide_pw(PA);
+    const int nt = (NA + 15) / 16;     // 16-monomial tiles
     const bool four = prm.K4 > 0;
     const WideLds L = wide_lds(K, PA, M, four, static_cast<int>(sizeof(T)));
     T* sC = reinterpret_cast<T*>(smem + L.coef);
@@ -189,14 +256,29 @@ __global__ __launch_bounds__(WT) void wide_kernel(WideArgs<T> g) {
     int* sTab = reinterpret_cast<int*>(smem + L.tab);
     T* sB = reinterpret_cast<T*>(smem + L.b);
     T* sS = reinterpret_cast<T*>(smem + L.s);
-    T* sR = reinterpret_cast<T*>(smem + L.r);      // [q][POD_MAX_K] R, then [q][POD_MAX_K] R'
-    T* sdR = sR + CH * POD_MAX_K;
-    T* sU = reinterpret_cast<T*>(smem + L.u);      // [q][4]: rhat, r
+    T* sPart = reinterpret_cast<T*>(smem + L.part);
+    T* sB0 = reinterpret_cast<T*>(smem + L.b0);
+    T* sR = reinterpret_cast<T*>(smem + L.r);      // [q][RS]: rhat, r, R_k (, R'_k)
     T* sP = reinterpret_cast<T*>(smem + L.pw);
+    __shared__ int sPartDef[WIDE_PARTS];
+    auto part_begin_of = [](int a) { return kParts.begin[a]; };   // parts of the degrees below a
+    T* sInv = reinterpret_cast<T*>(smem + L.inv);
+    T* sG4 = reinterpret_cast<T*>(smem + L.g);     // [wavefront][q][4]
+    float* sFact = reinterpret_cast<float*>(smem + L.fact);   // a! b! c!
     double* sRed = reinterpret_cast<double*>(smem + L.red);
     const int tid = threadIdx.x;
+    const int lane = tid % WAVE, wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int c16 = lane & 15, gq = lane >> 4;
 
-    for (int n = tid; n < NA; n += WT) sCode[n] = kWide.code[n];
+    if (tid <= POD_MAX_P) sInv[tid] = T(1) / T(tid > 0 ? tid : 1);
+    for (int n = tid; n < NA; n += WT) {
+        const int cd = kWide.code[n];
+        sCode[n] = cd;
+        float f = 1.0f;                // exact: at most 10!
+        for (int x = 0; x < 3; ++x)
+            for (int a = 2; a <= ((cd >> (4 * x)) & 15); ++a) f *= static_cast<float>(a);
+        sFact[n] = f;
+    }
     if (MODE == 1)
         for (int k = tid; k < M; k += WT) sC[k] = g.coef[k];
     if (four)
@@ -205,10 +287,24 @@ __global__ __launch_bounds__(WT) void wide_kernel(WideArgs<T> g) {
 
     const int K2 = prm.K2, K3 = prm.K3, K4 = prm.K4, P3 = prm.P3, P4 = prm.P4, KA = prm.Ka4;
     const int off3 = prm.off3, off4 = prm.off4;
-    // this thread's monomials in the basis pass
-    int mcode[MPT];
+    // parts: first and end monomial and degree
+    for (int a = 0; a < PA1; ++a) {
+        const int p0 = part_begin_of(a);
+        const int m0 = n_mono(a - 1), m1 = n_mono(a);
+        for (int x = tid; x < part_begin_of(a + 1) - p0; x += WT) {
+            const int x0 = m0 + x * PART_LEN;
+            sPartDef[p0 + x] = x0 | ((x0 + PART_LEN < m1 ? x0 + PART_LEN : m1) << 10) | (a << 20);
+        }
+    }
+    __syncthreads();
+    // power-table offsets of this lane's monomial of each of the wavefront's tiles
+    int moff[TPW];
 #pragma unroll
-    for (int j = 0; j < MPT; ++j) mcode[j] = (tid + j * WT < NA) ? sCode[tid + j * WT] : 0;
+    for (int j = 0; j < TPW; ++j) {
+        const int n = 16 * (wv + NWV * j) + c16;
+        const int cd = n < NA ? sCode[n] : 0;
+        moff[j] = (1 + (cd & 15)) | ((PA2 + 1 + ((cd >> 4) & 15)) << 8) | ((2 * PA2 + 1 + ((cd >> 8) & 15)) << 16);
+    }
 
     double gacc[DPT] = {0.0, 0.0};
     double eacc = 0.0;
@@ -217,83 +313,122 @@ __global__ __launch_bounds__(WT) void wide_kernel(WideArgs<T> g) {
     for (int c = 0; c < 9; ++c) vir[c] = 0.0;
     int eb = 0;
 
-    for (int i = blockIdx.x; i < g.N; i += gridDim.x) {
-        int b = g.offsets[i], e = g.offsets[i + 1];
-        if (b < 0 || e < b || e > g.P) {
+    const int RS = g.rs;
+    const int np = part_begin_of(PA1);
+    // list range of atom i (empty when malformed)
+    auto range = [&](int i, int& b, int& n) {
+        b = 0;
+        n = 0;
+        if (i >= g.N) return;
+        const int o0 = g.offsets[i], o1 = g.offsets[i + 1];
+        if (o0 < 0 || o1 < o0 || o1 > g.P) {
             eb |= ERR_NEIGH;
-            b = e = 0;
+            return;
         }
-        const int n = e - b;
-        const int RS = g.rs;
+        b = o0;
+        n = o1 - o0;
+    };
+    // the records of one chunk, NPRE values per thread, zero past its end
+    constexpr int NPRE = (CH * (4 + 2 * POD_MAX_K) + WT - 1) / WT;
+    T pre[NPRE];
+    auto request = [&](int p, int n) {
+        const int len = (n < CH ? n : CH) * RS;
+        const T* rc = g.rec + static_cast<size_t>(p) * RS;
+#pragma unroll
+        for (int x = 0; x < NPRE; ++x) {
+            const int t = tid + x * WT;
+            pre[x] = t < len ? rc[t] : T(0);
+        }
+    };
+    // records to LDS, then the divided powers of their unit vectors
+    auto stage = [&]() {
+#pragma unroll
+        for (int x = 0; x < NPRE; ++x) {
+            const int t = tid + x * WT;
+            if (t < CH * RS) sR[t] = pre[x];
+        }
+        __syncthreads();
+        if (tid < 3 * CH) {
+            const int q = tid / 3, ax = tid - 3 * q;
+            divided_powers(sP + q * PST + ax * PA2, sR[q * RS + ax], PA, sInv);
+        }
+        __syncthreads();
+    };
+
+    int b, n;
+    range(blockIdx.x, b, n);
+    request(b, n);
+    for (int i = blockIdx.x; i < g.N; i += gridDim.x) {
+        int bn, nn1;
+        range(i + static_cast<int>(gridDim.x), bn, nn1);
+        if (n == 0) __syncthreads();   // no stage() barrier before LDS is rewritten
 
         // ---- 1. atomic basis
-        T acc[MPT][POD_MAX_K];
+        typename Mx<T>::vec acc[TPW];
 #pragma unroll
-        for (int j = 0; j < MPT; ++j)
-#pragma unroll
-            for (int k = 0; k < POD_MAX_K; ++k) acc[j][k] = T(0);
+        for (int j = 0; j < TPW; ++j) acc[j] = typename Mx<T>::vec{T(0), T(0), T(0), T(0)};
         for (int c0 = 0; c0 < n; c0 += CH) {
-            const int nc = n - c0 < CH ? n - c0 : CH;
-            // stage the chunk: R_k of every pair, and the powers u_x^a, u_y^b,
-            // u_z^c of its unit vector
-            const T* rc = g.rec + static_cast<size_t>(b + c0) * RS;
-            for (int t = tid; t < nc * K; t += WT) {
-                const int q = t / K, k = t - q * K;
-                sR[q * POD_MAX_K + k] = rc[static_cast<size_t>(q) * RS + 4 + k];
+            if (c0 > 0) {
+                __syncthreads();   // the previous chunk is no longer read
+                request(b + c0, n - c0);
             }
-            for (int t = tid; t < nc * 3; t += WT) {
-                const int q = t / 3, ax = t - 3 * q;
-                const T u = rc[static_cast<size_t>(q) * RS + ax];
-                T* pw = sP + (q * 3 + ax) * PA1;
-                T v = T(1);
-                for (int a = 0; a <= PA; ++a) {
-                    pw[a] = v;
-                    v *= u;
-                }
-            }
-            __syncthreads();
+            stage();
+            const int nq = n - c0 < CH ? n - c0 : CH;
 #pragma unroll 1
-            for (int q = 0; q < nc; ++q) {
-                const T* pw = sP + q * 3 * PA1;
-                const T* Rq = sR + q * POD_MAX_K;
-                T Rv[POD_MAX_K];
+            for (int q0 = 0; q0 < nq; q0 += 4) {
+                const int q = q0 + gq;
+                const T Rk = c16 < K ? sR[q * RS + 4 + c16] : T(0);
+                const T* pw = sP + q * PST;
 #pragma unroll
-                for (int k = 0; k < POD_MAX_K; ++k) Rv[k] = k < K ? Rq[k] : T(0);
+                for (int j = 0; j < TPW; ++j)
+                    if (wv + NWV * j < nt)
+                        acc[j] = Mx<T>::mul(Rk, pw[moff[j] & 255] * pw[(moff[j] >> 8) & 255] * pw[moff[j] >> 16], acc[j]);
+            }
+        }
+        // the next atom's records, in flight until its stage()
+        if (n <= CH) request(bn, nn1);
 #pragma unroll
-                for (int j = 0; j < MPT; ++j) {
-                    if (tid + j * WT < NA) {
-                        const int cd = mcode[j];
-                        const T A = pw[cd & 15] * pw[PA1 + ((cd >> 4) & 15)] * pw[2 * PA1 + ((cd >> 8) & 15)];
+        for (int j = 0; j < TPW; ++j) {
+            const int nn = 16 * (wv + NWV * j) + c16;
+            if (nn < NA) {
+                const T f = T(sFact[nn]);
 #pragma unroll
-                        for (int k = 0; k < POD_MAX_K; ++k) acc[j][k] += Rv[k] * A;
-                    }
+                for (int e4 = 0; e4 < 4; ++e4) {
+                    const int k = Mx<T>::row(gq, e4);
+                    if (k < K) sB[k * NR + nn] = acc[j][e4] * f;
                 }
             }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int j = 0; j < MPT; ++j) {
-            const int nn = tid + j * WT;
-            if (nn < NA)
-#pragma unroll
-                for (int k = 0; k < POD_MAX_K; ++k)
-                    if (k < K) sB[k * NA + nn] = acc[j][k];
         }
         __syncthreads();
 
-        // ---- 2. degree sums and descriptors
-        for (int w = tid; w < K * PA1; w += WT) {
-            const int k = w / PA1, a = w - k * PA1;
-            const int n0 = n_mono(a - 1), n1 = n_mono(a);
-            const T* Bk = sB + k * NA;
+        // ---- 2. parts of the degree sums; without 4-body terms the adjoint row
+        // entries too (3.), which then depend on their own basis entry only
+        const bool own_adj = MODE == 1 && !four && g.want_back;
+        for (int t = tid; t < K * np; t += WT) {
+            const int k = t / np, pt = t - k * np;
+            const int pc = sPartDef[pt];
+            const int a = pc >> 20, n0 = pc & 1023, n1 = (pc >> 10) & 1023;
+            T* Bk = sB + k * NR;
             T s = T(0);
+            const T c3 = own_adj && k < K3 && a <= P3 ? T(2) * sC[off3 + k * (P3 + 1) + a] : T(0);
             for (int nn = n0; nn < n1; ++nn) {
-                const T v = Bk[nn];
-                s += T(sCode[nn] >> 16) * v * v;
+                const T v = Bk[nn], mv = T(sCode[nn] >> 16) * v;
+                s += mv * v;
+                if (own_adj) Bk[nn] = (c3 * mv + (nn == 0 && k < K2 ? sC[1 + k] : T(0))) * T(sFact[nn]);
+                if (nn == 0) sB0[k] = v;
             }
-            sS[w] = s;
+            sPart[k * WIDE_PARTS + pt] = s;
         }
         __syncthreads();
+        auto degree_sum = [&](int k, int a) {
+            T s = T(0);
+            for (int pt = part_begin_of(a); pt < part_begin_of(a + 1); ++pt) s += sPart[k * WIDE_PARTS + pt];
+            return s;
+        };
+        if (four) {
+            for (int w = tid; w < K * PA1; w += WT) sS[w] = degree_sum(w / PA1, w % PA1);
+            __syncthreads();
+        }
         double ep = 0.0;
 #pragma unroll
         for (int j = 0; j < DPT; ++j) {
@@ -303,13 +438,13 @@ __global__ __launch_bounds__(WT) void wide_kernel(WideArgs<T> g) {
             if (dc == 0) {
                 v = T(1);
             } else if (dc < off3) {
-                v = sB[(dc - 1) * NA];
+                v = sB0[dc - 1];
             } else if (dc < off4) {
                 const int k = (dc - off3) / (P3 + 1), a = (dc - off3) - k * (P3 + 1);
-                v = sS[k * PA1 + a];
+                v = degree_sum(k, a);
             } else {
                 const int k = (dc - off4) / KA, p = (dc - off4) - k * KA;
-                const T* Bk = sB + k * NA;
+                const T* Bk = sB + k * NR;
                 const int tri = sTab[T_PTRI + p];
                 if ((tri >> 4) == 0) {
                     v = Bk[0] * sS[k * PA1 + (tri & 15)];                           // eq. (27a)
@@ -336,27 +471,19 @@ __global__ __launch_bounds__(WT) void wide_kernel(WideArgs<T> g) {
                 gacc[j] += static_cast<double>(v);
             }
         }
-        if constexpr (MODE == 0) {
-            __syncthreads();   // sB and sS are rewritten by the next atom
-            continue;
-        } else {
-            const double Ei = block_sum(ep, sRed);
-            if (tid == 0) {
-                if (g.E_atom) g.E_atom[i] = static_cast<T>(Ei);
-                eacc += Ei;
-            }
-            if (!g.want_back) {
-                __syncthreads();
-                continue;
-            }
-
+        if constexpr (MODE == 1) {
+            ep = wave_sum(ep);
+            if (lane == 0) sRed[wv] = ep;
+            if (!g.want_back) __syncthreads();
+        }
+        if (MODE == 1 && g.want_back) {
             // ---- 3. adjoint dE_i/dB_{k n}, one radial index at a time: the
             // contractions are diagonal in k, so row k of the adjoint needs
             // only row k of the basis and overwrites it in place
             const T* cf = sC;
 #pragma unroll 1
-            for (int k = 0; k < K; ++k) {
-                T* Bk = sB + k * NA;
+            for (int k = 0; four && k < K; ++k) {
+                T* Bk = sB + k * NR;
                 const T B0 = Bk[0];
                 T ab[MPT];
 #pragma unroll
@@ -404,110 +531,129 @@ __global__ __launch_bounds__(WT) void wide_kernel(WideArgs<T> g) {
                 __syncthreads();   // every read of row k is done
 #pragma unroll
                 for (int j = 0; j < MPT; ++j)
-                    if (tid + j * WT < NA) Bk[tid + j * WT] = ab[j];
+                    if (tid + j * WT < NA) Bk[tid + j * WT] = ab[j] * T(sFact[tid + j * WT]);
             }
-            __syncthreads();
-            const T* sA = sB;   // adjoint rows [K][NA]
+            if (four) __syncthreads();
+            const T* sA = sB;   // adjoint rows [K][NR], times a! b! c!
 
             // ---- 4. pair gradients, eq. (24c)
-            const int q = tid / GSUB, s = tid - q * GSUB;
             for (int c0 = 0; c0 < n; c0 += CH) {
                 const int nc = n - c0 < CH ? n - c0 : CH;
-                const T* rc = g.rec + static_cast<size_t>(b + c0) * RS;
-                for (int t = tid; t < nc * K; t += WT) {
-                    const int qq = t / K, k = t - qq * K;
-                    sR[qq * POD_MAX_K + k] = rc[static_cast<size_t>(qq) * RS + 4 + k];
-                    sdR[qq * POD_MAX_K + k] = rc[static_cast<size_t>(qq) * RS + 4 + K + k];
+                const int nq = (nc + 15) & ~15;
+                if (n > CH) {
+                    __syncthreads();
+                    request(b + c0, n - c0);
+                    stage();
                 }
-                for (int t = tid; t < nc * 4; t += WT) {
-                    const int qq = t / 4, c = t - 4 * qq;
-                    const T v = rc[static_cast<size_t>(qq) * RS + c];
-                    sU[qq * 4 + c] = v;
-                    if (c < 3) {
-                        T* pw = sP + (qq * 3 + c) * PA1;
-                        T x = T(1);
-                        for (int a = 0; a <= PA; ++a) {
-                            pw[a] = x;
-                            x *= v;
-                        }
-                    }
-                }
-                __syncthreads();
-                const bool in = q < nc;
-                const int p = b + c0 + q;
-                const int qc = in ? q : 0;
-                const T u[3] = {sU[qc * 4 + 0], sU[qc * 4 + 1], sU[qc * 4 + 2]};
-                const T r = sU[qc * 4 + 3];
-                const T ri = T(1) / r;
-                const bool ok = in && (u[0] * u[0] + u[1] * u[1] + u[2] * u[2] > T(0.5));
-                T R[POD_MAX_K], dR[POD_MAX_K];
+                for (int qt = 0; qt < nq; qt += 16) {
+                    const int q = qt + c16;
+                    const T* pw = sP + q * PST;
+                    T Rk[KSTEP], dRk[KSTEP];
 #pragma unroll
-                for (int k = 0; k < POD_MAX_K; ++k) {
-                    R[k] = k < K ? sR[qc * POD_MAX_K + k] : T(0);
-                    dR[k] = k < K ? sdR[qc * POD_MAX_K + k] : T(0);
-                }
-                const T* pw = sP + qc * 3 * PA1;
-                T sa = T(0), gv0 = T(0), gv1 = T(0), gv2 = T(0);
+                    for (int s = 0; s < KSTEP; ++s) {
+                        const int k = 4 * s + gq;
+                        Rk[s] = k < K ? sR[q * RS + 4 + k] : T(0);
+                        dRk[s] = k < K ? sR[q * RS + 4 + K + k] : T(0);
+                    }
+                    T sa = T(0), gv0 = T(0), gv1 = T(0), gv2 = T(0);
 #pragma unroll 1
-                for (int nn = s; nn < NA; nn += GSUB) {
-                    const int cd = sCode[nn];
-                    const int ea = cd & 15, ebx = (cd >> 4) & 15, ec = (cd >> 8) & 15, dg = (cd >> 12) & 15;
-                    const T xa = pw[ea], yb = pw[PA1 + ebx], zc = pw[2 * PA1 + ec];
-                    T w1 = T(0), w2 = T(0);
+                    for (int tl = wv; tl < nt; tl += NWV) {
+                        typename Mx<T>::vec w1{T(0), T(0), T(0), T(0)}, w2{T(0), T(0), T(0), T(0)};
+                        const int na = 16 * tl + c16;
 #pragma unroll
-                    for (int k = 0; k < POD_MAX_K; ++k) {
-                        if (k < K) {
-                            const T av = sA[k * NA + nn];
-                            w1 += av * dR[k];
-                            w2 += av * R[k];
+                        for (int s = 0; s < KSTEP; ++s) {
+                            const int k = 4 * s + gq;
+                            const T av = k < K && na < NA ? sA[k * NR + na] : T(0);
+                            w1 = Mx<T>::mul(av, dRk[s], w1);
+                            w2 = Mx<T>::mul(av, Rk[s], w2);
+                        }
+#pragma unroll
+                        for (int e4 = 0; e4 < 4; ++e4) {
+                            const int nn = 16 * tl + Mx<T>::row(gq, e4);
+                            const int cd = sCode[nn < NA ? nn : 0];   // past the end W = 0
+                            const T* px = pw + (cd & 15);
+                            const T* py = pw + PA2 + ((cd >> 4) & 15);
+                            const T* pz = pw + 2 * PA2 + ((cd >> 8) & 15);
+                            const T xm = px[0], xa = px[1], ym = py[0], yb = py[1], zm = pz[0], zc = pz[1];
+                            const T yz = yb * zc;
+                            sa += w1[e4] * (xa * yz);
+                            gv0 += w2[e4] * (xm * yz);
+                            gv1 += w2[e4] * (ym * (xa * zc));
+                            gv2 += w2[e4] * (zm * (xa * yb));
                         }
                     }
-                    const T A = xa * yb * zc;
-                    sa += (w1 - T(dg) * ri * w2) * A;
-                    if (ea > 0) gv0 += w2 * T(ea) * pw[ea - 1] * yb * zc;
-                    if (ebx > 0) gv1 += w2 * T(ebx) * xa * pw[PA1 + ebx - 1] * zc;
-                    if (ec > 0) gv2 += w2 * T(ec) * xa * yb * pw[2 * PA1 + ec - 1];
-                }
-                // sum over the eight lanes of the pair (fixed order)
+                    // sum over the pair's four lanes (fixed order)
 #pragma unroll
-                for (int o = 1; o < GSUB; o <<= 1) {
-                    sa += __shfl_xor(sa, o);
-                    gv0 += __shfl_xor(gv0, o);
-                    gv1 += __shfl_xor(gv1, o);
-                    gv2 += __shfl_xor(gv2, o);
-                }
-                const T gx = ok ? sa * u[0] + ri * gv0 : T(0);
-                const T gy = ok ? sa * u[1] + ri * gv1 : T(0);
-                const T gz = ok ? sa * u[2] + ri * gv2 : T(0);
-                if (s == 0 && in) {
-                    if (g.gown) {
-                        T* go = g.gown + 3 * static_cast<size_t>(p);
-                        go[0] = gx; go[1] = gy; go[2] = gz;
-                    } else if (ok && g.Facc) {
-                        const int j = g.nbr_j[p];
-                        atomicAdd(&g.Facc[3 * j + 0], -static_cast<double>(gx));
-                        atomicAdd(&g.Facc[3 * j + 1], -static_cast<double>(gy));
-                        atomicAdd(&g.Facc[3 * j + 2], -static_cast<double>(gz));
-                        atomicAdd(&g.Facc[3 * i + 0], static_cast<double>(gx));
-                        atomicAdd(&g.Facc[3 * i + 1], static_cast<double>(gy));
-                        atomicAdd(&g.Facc[3 * i + 2], static_cast<double>(gz));
+                    for (int o = 16; o < WAVE; o <<= 1) {
+                        sa += __shfl_xor(sa, o);
+                        gv0 += __shfl_xor(gv0, o);
+                        gv1 += __shfl_xor(gv1, o);
+                        gv2 += __shfl_xor(gv2, o);
                     }
-                    if (ok) {
-                        const double dd[3] = {static_cast<double>(u[0] * r), static_cast<double>(u[1] * r),
-                                              static_cast<double>(u[2] * r)};
-                        const double gg[3] = {static_cast<double>(gx), static_cast<double>(gy),
-                                              static_cast<double>(gz)};
-#pragma unroll
-                        for (int x = 0; x < 3; ++x)
-#pragma unroll
-                            for (int y = 0; y < 3; ++y) vir[3 * x + y] -= dd[x] * gg[y];
+                    if (gq == 0) {
+                        T* o4 = sG4 + (wv * CH + q) * 4;
+                        o4[0] = sa; o4[1] = gv0; o4[2] = gv1; o4[3] = gv2;
                     }
                 }
-                __syncthreads();   // the chunk's staging is rewritten next
+                // read before the barrier: the next stage() may overwrite the records
+                const int q = tid < CH ? tid : 0, p = b + c0 + q;
+                const T u[3] = {sR[q * RS + 0], sR[q * RS + 1], sR[q * RS + 2]};
+                const T r = sR[q * RS + 3];
+                __syncthreads();
+                if (tid < nc) {
+                    const T ri = T(1) / r;
+                    const bool ok = u[0] * u[0] + u[1] * u[1] + u[2] * u[2] > T(0.5);
+                    T sm[4];
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        sm[x] = (sG4[q * 4 + x] + sG4[(CH + q) * 4 + x]) +
+                                (sG4[(2 * CH + q) * 4 + x] + sG4[(3 * CH + q) * 4 + x]);
+                    const T gv0 = sm[1], gv1 = sm[2], gv2 = sm[3];
+                    const T sa = sm[0] - (u[0] * gv0 + u[1] * gv1 + u[2] * gv2) * ri;
+                    const T gx = ok ? sa * u[0] + ri * gv0 : T(0);
+                    const T gy = ok ? sa * u[1] + ri * gv1 : T(0);
+                    const T gz = ok ? sa * u[2] + ri * gv2 : T(0);
+                    {
+                        if (g.gown) {
+                            T* go = g.gown + 3 * static_cast<size_t>(p);
+                            go[0] = gx; go[1] = gy; go[2] = gz;
+                        } else if (ok && g.Facc) {
+                            const int j = g.nbr_j[p];
+                            atomicAdd(&g.Facc[3 * j + 0], -static_cast<double>(gx));
+                            atomicAdd(&g.Facc[3 * j + 1], -static_cast<double>(gy));
+                            atomicAdd(&g.Facc[3 * j + 2], -static_cast<double>(gz));
+                            atomicAdd(&g.Facc[3 * i + 0], static_cast<double>(gx));
+                            atomicAdd(&g.Facc[3 * i + 1], static_cast<double>(gy));
+                            atomicAdd(&g.Facc[3 * i + 2], static_cast<double>(gz));
+                        }
+                        if (ok) {
+                            const double dd[3] = {static_cast<double>(u[0] * r), static_cast<double>(u[1] * r),
+                                                  static_cast<double>(u[2] * r)};
+                            const double gg[3] = {static_cast<double>(gx), static_cast<double>(gy),
+                                                  static_cast<double>(gz)};
+    #pragma unroll
+                            for (int x = 0; x < 3; ++x)
+    #pragma unroll
+                                for (int y = 0; y < 3; ++y) vir[3 * x + y] -= dd[x] * gg[y];
+                        }
+                    }
+                }
             }
-            __syncthreads();   // LDS is rewritten by the next atom
         }
+        if constexpr (MODE == 1) {
+            // sRed was written before the last barrier
+            if (n == 0 && g.want_back) __syncthreads();
+            if (tid == 0) {
+                const double Ei = (sRed[0] + sRed[1]) + (sRed[2] + sRed[3]);
+                if (g.E_atom) g.E_atom[i] = static_cast<T>(Ei);
+                eacc += Ei;
+            }
+        }
+        if (n > CH) request(bn, nn1);
+        b = bn;
+        n = nn1;
     }
+    if constexpr (MODE == 1) __syncthreads();
 
     // block partials (every thread takes part in the reductions)
     const int blk = blockIdx.x, nblk = gridDim.x;
