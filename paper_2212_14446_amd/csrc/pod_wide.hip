@@ -236,12 +236,10 @@ __global__ __launch_bounds__(WT) void wide_pair_kernel(WideArgs<T> g) {
     if ((tid & 63) == 0 && eb) atomicOr(g.err, eb);
 }
 
-// Wavefronts per SIMD: the LDS allows three workgroups of the energy kernel per
-// compute unit.
-constexpr int wide_waves(int mode) { return mode == 0 ? 4 : 2; }
-
-template <typename T, int MODE>
-__global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(wide_waves(MODE)))) void wide_kernel(WideArgs<T> g) {
+// VL: the virial's sums in LDS (one column per thread of the gradient's end)
+// instead of 18 registers of every thread.
+template <typename T, int MODE, bool VL>
+__device__ __forceinline__ void wide_body(const WideArgs<T>& g) {
     extern __shared__ __align__(16) unsigned char smem[];
     const ParamsT<T>& prm = g.prm;
     const int K = prm.K, PA = prm.PA, M = prm.M;
@@ -308,9 +306,14 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(wide_waves(M
 
     double gacc[DPT] = {0.0, 0.0};
     double eacc = 0.0;
-    double vir[9];
+    __shared__ double sVir[VL ? 9 * CH : 1];
+    double vir[VL ? 1 : 9];
+    if constexpr (VL) {
+        for (int t = tid; t < 9 * CH; t += WT) sVir[t] = 0.0;
+    } else {
 #pragma unroll
-    for (int c = 0; c < 9; ++c) vir[c] = 0.0;
+        for (int c = 0; c < 9; ++c) vir[c] = 0.0;
+    }
     int eb = 0;
 
     const int RS = g.rs;
@@ -634,7 +637,10 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(wide_waves(M
     #pragma unroll
                             for (int x = 0; x < 3; ++x)
     #pragma unroll
-                                for (int y = 0; y < 3; ++y) vir[3 * x + y] -= dd[x] * gg[y];
+                                for (int y = 0; y < 3; ++y) {
+                                if constexpr (VL) sVir[(3 * x + y) * CH + tid] -= dd[x] * gg[y];
+                                else vir[3 * x + y] -= dd[x] * gg[y];
+                            }
                         }
                     }
                 }
@@ -669,7 +675,9 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(wide_waves(M
         if (g.want_W) {
 #pragma unroll
             for (int c = 0; c < 9; ++c) {
-                const double v = block_sum(vir[c], sRed);
+                double v;
+                if constexpr (VL) v = block_sum(tid < CH ? sVir[c * CH + tid] : 0.0, sRed);
+                else v = block_sum(vir[c], sRed);
                 if (tid == 0) g.wpart[static_cast<size_t>(c) * nblk + blk] = v;
                 __syncthreads();
             }
@@ -677,6 +685,22 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(wide_waves(M
     }
     eb = wave_or(eb);
     if ((tid & 63) == 0 && eb) atomicOr(g.err, eb);
+}
+
+// Wavefronts per SIMD.  The energy kernel of a model whose LDS lets three
+// workgroups share a compute unit is held to three (K = 10, P3 = 8 FP64: 526 ->
+// 451 us, K = 12, P3 = 10 FP32: 473 -> 406 us); with K = 12, P3 = 10 in FP64 only
+// two fit, and the same kernel took 793 us against 753.
+constexpr int wide_waves(int mode) { return mode == 0 ? 4 : 2; }
+
+template <typename T, int MODE>
+__global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(wide_waves(MODE)))) void wide_kernel(WideArgs<T> g) {
+    wide_body<T, MODE, false>(g);
+}
+
+template <typename T>
+__global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(3))) void wide_kernel_occ3(WideArgs<T> g) {
+    wide_body<T, 1, true>(g);
 }
 
 template <typename T, int MODE>
@@ -690,7 +714,11 @@ hipError_t launch_mode(const WideArgs<T>& a, bool fast, int nblk, hipStream_t st
         if (e != hipSuccess) return e;
     }
     const size_t lds = wide_lds(a.prm.K, a.prm.PA, a.prm.M, a.prm.K4 > 0, static_cast<int>(sizeof(T))).total;
-    hipLaunchKernelGGL((wide_kernel<T, MODE>), dim3(nblk), dim3(WT), lds, st, a);
+    constexpr size_t STATIC = WIDE_PARTS * sizeof(int) + 9 * CH * sizeof(double);
+    if (MODE == 1 && lds + STATIC <= 163840 / 3)
+        hipLaunchKernelGGL((wide_kernel_occ3<T>), dim3(nblk), dim3(WT), lds, st, a);
+    else
+        hipLaunchKernelGGL((wide_kernel<T, MODE>), dim3(nblk), dim3(WT), lds, st, a);
     return hipGetLastError();
 }
 
