@@ -26,10 +26,12 @@
 // reverse_kernel  builds the reverse-pair index of a list once.
 // Models beyond these kernels' register budget (angular degree above
 // FAST_MAX_PA or more than FAST_MAX_K radial functions) run the whole
-// energy path in the wide-degree kernel of pod_wide.hip, whose partials and
-// pair gradients have the same layout, so finalize_kernel serves both.
+// energy path in the wide-degree kernel of pod_wide.hip, and small systems
+// run it in one workgroup per atom (pod_small.hip); their partials and pair
+// gradients have the same layout, so finalize_kernel serves all.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <mutex>
@@ -37,6 +39,7 @@
 #include "pod.h"
 #include "pod_device.h"
 #include "pod_net.h"
+#include "pod_small.h"
 #include "pod_internal.h"
 #include "pod_tables.h"
 #include "pod_wide.h"
@@ -1115,6 +1118,13 @@ int descriptors_impl(pod_handle* h, int N, int P, const void* pos, const double*
         timing_end(h, 1);
         return e == hipSuccess ? POD_OK : POD_EHIP;
     }
+    if (small_path(h->K, h->PA, N)) {
+        const WideArgs<T> w = wide_args(a);
+        timing_begin(h, 1);
+        const hipError_t e = launch_small<T>(w, h->PA, 0, h->std_ok != 0, h->stream);
+        timing_end(h, 1);
+        return e == hipSuccess ? POD_OK : POD_EHIP;
+    }
     const int apw = WAVE / h->K;
     const int nblk = (N + apw - 1) / apw;
     timing_begin(h, 1);
@@ -1135,11 +1145,14 @@ struct EfScratch {
     size_t part, wpart, abar, centre, pdv, gown, rec, total;
 };
 
-EfScratch ef_scratch_layout(int N, int P, int K, int PA, int M, size_t tsize, bool back, bool gather) {
+EfScratch ef_scratch_layout(int N, int P, int K, int PA, int M, size_t tsize, bool back, bool gather, bool net) {
     auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
-    const bool wide = wide_path(K, PA);   // one kernel, partials per persistent workgroup
+    const bool small = !net && small_path(K, PA, N);   // partials per atom, pair gradients only
+    const bool wide = small || wide_path(K, PA);             // one kernel, partials per persistent workgroup
     const int apw = WAVE / K;
-    const size_t nblk = N <= 0 ? 0 : wide ? static_cast<size_t>(wide_blocks(N)) : (static_cast<size_t>(N) + apw - 1) / apw;
+    const size_t nblk = N <= 0 ? 0 : small ? static_cast<size_t>(N)
+                                   : wide  ? static_cast<size_t>(wide_blocks(N))
+                                           : (static_cast<size_t>(N) + apw - 1) / apw;
     const size_t nblk_p = !back ? 0 : wide ? nblk : (static_cast<size_t>(P) + PAIR_BLOCK - 1) / PAIR_BLOCK;
     EfScratch L;
     size_t o = 0;
@@ -1150,7 +1163,7 @@ EfScratch ef_scratch_layout(int N, int P, int K, int PA, int M, size_t tsize, bo
     L.centre = o; o += wide ? 0 : al((static_cast<size_t>(P) + 1) * sizeof(int));   // entry P: spare for empty slots
     L.pdv = o; o += wide ? 0 : al((static_cast<size_t>(P) + 1) * 3 * tsize);
     L.gown = o; o += gather ? al(static_cast<size_t>(P > 0 ? P : 1) * 3 * tsize) : 0;
-    L.rec = o; o += wide ? al(static_cast<size_t>(P > 0 ? P : 1) * wide_rec_stride(K, true) * tsize) : 0;
+    L.rec = o; o += wide && !small ? al(static_cast<size_t>(P > 0 ? P : 1) * wide_rec_stride(K, true) * tsize) : 0;
     L.total = o;
     return L;
 }
@@ -1171,7 +1184,7 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
     const bool back = (F != nullptr) || (W != nullptr);
     const bool gather = rev != nullptr && F != nullptr;
     const int nblk_p = back ? (P + PAIR_BLOCK - 1) / PAIR_BLOCK : 0;
-    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather);
+    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, MODE == 2);
     a.coef = static_cast<const T*>(c);
     a.E_atom = static_cast<T*>(E_atom);
     a.part = reinterpret_cast<double*>(scratch + L.part);
@@ -1181,11 +1194,13 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
     a.want_G = G != nullptr;
     a.want_back = back;
     a.netw = netw; a.n_net = n_net;
-    if (wide_path(h->K, h->PA)) {
+    const bool small = MODE == 1 && small_path(h->K, h->PA, N);
+    if (small || wide_path(h->K, h->PA)) {
         if constexpr (MODE != 1) return POD_ENOTSUP;
-        // wide-degree kernel: energy, G and pair gradients in one launch
+        // wide-degree kernel, or one workgroup per atom of a small system:
+        // energy, G and pair gradients in one launch
         WideArgs<T> w = wide_args(a);
-        const int nblk_w = wide_blocks(N);
+        const int nblk_w = small ? N : wide_blocks(N);
         w.wpart = reinterpret_cast<double*>(scratch + L.wpart);
         w.gown = gather ? reinterpret_cast<T*>(scratch + L.gown) : nullptr;
         w.Facc = (back && !gather) ? facc : nullptr;
@@ -1193,7 +1208,8 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
         w.rs = wide_rec_stride(h->K, true);
         w.want_W = W != nullptr;
         timing_begin(h, 1);
-        const hipError_t e = launch_wide<T>(w, 1, h->std_ok != 0, nblk_w, h->stream);
+        const hipError_t e = small ? launch_small<T>(w, h->PA, 1, h->std_ok != 0, h->stream)
+                                   : launch_wide<T>(w, 1, h->std_ok != 0, nblk_w, h->stream);
         timing_end(h, 1);
         if (e != hipSuccess) return POD_EHIP;
         FinArgs<T> fa;
@@ -1268,7 +1284,7 @@ int energy_forces_impl(pod_handle* h, int N, int P, const void* pos, const doubl
                        int n_net = 0) {
     const bool back = (F != nullptr) || (W != nullptr);
     const bool gather = rev != nullptr && F != nullptr;
-    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather);
+    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, MODE == 2);
     int rc = ensure_scratch(h, L.total);
     if (rc != POD_OK) return rc;
     rc = ensure_force_acc(h, N);
@@ -1312,10 +1328,16 @@ int energy_forces_noalloc_impl(pod_handle* h, int N, int P, const void* pos, con
                                void* E_atom, double* E, void* F, double* W, double* G) {
     const bool back = (F != nullptr) || (W != nullptr);
     const bool gather = rev != nullptr && F != nullptr;
-    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather);
+    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, false);
     const size_t facc_bytes = (back && !gather) ? ((static_cast<size_t>(N) * 3 * sizeof(double) + 255) & ~size_t(255))
                                                 : 0;
-    if (L.total + facc_bytes > static_cast<size_t>(POD_STATIC_SCRATCH_BYTES)) return POD_ETOOBIG;
+    // What a call may need is part of the interface: the per-atom and pair
+    // kernels' arrays with the gradients at two slots per pair, whichever
+    // kernels take the call.
+    const EfScratch full = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, true);
+    const size_t second = gather ? (static_cast<size_t>(P > 0 ? P : 1) * 3 * sizeof(T) + 255) & ~size_t(255) : 0;
+    if (std::max(L.total, full.total + second) + facc_bytes > static_cast<size_t>(POD_STATIC_SCRATCH_BYTES))
+        return POD_ETOOBIG;
     if (h->device < 0 || h->device >= MAX_DEVICES) return POD_EHIP;
     char* base;
     {
