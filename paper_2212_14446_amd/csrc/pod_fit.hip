@@ -31,8 +31,11 @@ constexpr int GRAM_BLOCKS = 512;       // persistent: two workgroups per CU
 constexpr int GRAM_ROWS = 32;          // rows per LDS chunk (8 MFMA k-steps)
 constexpr int RED_SLICES = 16;         // first reduction pass: workgroup partials in 16 slices
 constexpr int FIT_MAX_TILES = 8;       // M + 1 <= 128
-constexpr int SOLVE_THREADS = 256;      // a 16 x 16 grid in the Cholesky update
-static_assert(SOLVE_THREADS == 256, "solve_kernel maps its threads to a 16 x 16 grid");
+constexpr int SOLVE_THREADS = 512;      // two waves per SIMD, 256 registers each
+constexpr int SOLVE_MAX_M = 2 * WAVE;   // two right-hand-side rows per lane
+static_assert(SOLVE_THREADS >= 4 * SOLVE_MAX_M, "four lanes per row of Z c");
+constexpr int SOLVE_ROWS = SOLVE_THREADS / SOLVE_MAX_M;   // rows of Z loaded per turn, one column a thread
+constexpr int SOLVE_Z = (SOLVE_MAX_M + SOLVE_ROWS) / SOLVE_ROWS;   // turns for M + 1 rows
 
 // Upper-triangle tile pairs (ti <= tj) of a T x T tiling, row by row; pair
 // p belongs to wave p % GRAM_WAVES.
@@ -256,107 +259,148 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(ReduceArgs a) {
 // loss = c^T Z_AA c - 2 c^T Z_Ab + Z_bb + gamma c^T c, the value of eq. (63a).
 //
 // Factorisation: blocked right-looking Cholesky with panels of 16 columns
-// (three barriers per panel).  The two triangular solves run in wave 0 with
-// the right-hand side in registers (lane l holds rows l and l + 64) and the
-// pivot value broadcast by readlane, so they need no barriers.
+// (three barriers per panel).  The right-hand side is one more row below the
+// matrix, so the factorisation leaves L^-1 b in it and no forward sweep is
+// left.  Wave 0 factors a diagonal block in registers (lane r holds row r,
+// pivots and columns broadcast by readlane); the back substitution runs in
+// wave 0 with the right-hand side in registers (lane l holds rows l and
+// l + 64) and the factor's rows read eight steps ahead, so it needs no barrier.
+// Z is read once, every load in flight together, and stays in registers for
+// the objective.
+// Bound by the serial chain of M pivots and M back-substitution steps:
+// M = 103 144 -> 64 us (before: 256 threads, Z read twice, diagonal
+// blocks and both sweeps through LDS).
 __global__ __launch_bounds__(SOLVE_THREADS) void solve_kernel(int M, const double* __restrict__ Z, double gamma,
                                                               double* __restrict__ c, double* __restrict__ loss,
                                                               int* err) {
     extern __shared__ double lds[];
-    const int D = M + 1;             // Z is D x D; S keeps Z's row stride
-    double* S = lds;                 // D x D
-    double* sc = S + D * D;          // M: 1 / sqrt(diag of the unscaled matrix)
-    double* ipiv = sc + M;           // M: 1 / sqrt(pivot)
+    const int D = M + 1;             // Z is D x D
+    const int DS = D | 1;            // row stride in LDS (odd: columns without bank conflicts)
+    double* S = lds;                 // D x DS: the matrix, below it the right-hand side
+    double* sc = S + D * DS;         // M: 1 / sqrt(diag of the unscaled matrix)
+    double* ipiv = sc + M;           // M: 1 / L_kk
     double* cv = ipiv + M;           // M: solution
     __shared__ int bad;
+    __shared__ double red[SOLVE_THREADS / WAVE];
     const int tid = threadIdx.x;
-    const int ty = tid >> 4, tx = tid & 15;
+    const int lane = tid & (WAVE - 1), wave = tid / WAVE;
     if (tid == 0) bad = 0;
-#pragma unroll 4
-    for (int e = tid; e < M * D; e += SOLVE_THREADS) S[e] = Z[e];
+    // columns 0 ... M - 1 of all rows (row M is the right-hand side)
+    const int zr = tid / SOLVE_MAX_M, zc = tid % SOLVE_MAX_M;
+    double z[SOLVE_Z];
+#pragma unroll
+    for (int q = 0; q < SOLVE_Z; ++q) {
+        const int i = zr + q * SOLVE_ROWS;
+        z[q] = i <= M && zc < M ? Z[i * D + zc] : 0.0;
+    }
+    const double zbb = Z[M * D + M];
+    for (int i = tid; i < M; i += SOLVE_THREADS) sc[i] = Z[i * D + i];
     __syncthreads();
-    for (int i = tid; i < M; i += SOLVE_THREADS) {
-        const double d = S[i * D + i] + gamma;
+    if (tid < M) {
+        const double d = sc[tid] + gamma;
         if (!(d > 0.0) || !isfinite(d)) {
             bad = 1;
-            sc[i] = 0.0;
+            sc[tid] = 0.0;
         } else {
-            sc[i] = 1.0 / sqrt(d);
+            sc[tid] = 1.0 / sqrt(d);
         }
     }
     __syncthreads();
-    // scaled lower triangle and right-hand side (column M)
-    for (int i = ty; i < M; i += 16) {
-        const double si = sc[i];
-        for (int j = tx; j <= i; j += 16) S[i * D + j] = (S[i * D + j] + (i == j ? gamma : 0.0)) * si * sc[j];
-        if (tx == 0) S[i * D + M] *= si;
+    // scaled matrix, below it the scaled right-hand side
+    if (zc < M) {
+        const double sj = sc[zc];
+#pragma unroll
+        for (int q = 0; q < SOLVE_Z; ++q) {
+            const int i = zr + q * SOLVE_ROWS;
+            if (i <= M) S[i * DS + zc] = (z[q] + (i == zc ? gamma : 0.0)) * (i < M ? sc[i] : 1.0) * sj;
+        }
     }
     __syncthreads();
     // blocked right-looking Cholesky, panels of 16 columns, lower triangle:
-    // (1) wave 0 factors the diagonal block (its LDS operations execute in
-    // order, so wavefront fences suffice between the steps), (2) one thread
-    // per row below solves the panel against it, (3) the trailing triangle
-    // takes the rank-16 update -- three barriers per panel
+    // (1) wave 0 factors the diagonal block, (2) one thread per row below
+    // solves the panel against it, (3) the trailing triangle takes the rank-16
+    // update -- three barriers per panel
     for (int k0 = 0; k0 < M; k0 += 16) {
         const int kb = M - k0 < 16 ? M - k0 : 16;
         if (tid < WAVE) {
-            const int r = tid & 15, cg = tid >> 4;   // row r of the block, columns 4 cg .. 4 cg + 3
-            for (int k = 0; k < kb; ++k) {
-                const double d = S[(k0 + k) * D + k0 + k];
-                if (!(d > 0.0) || !isfinite(d)) {   // the same value in every lane
-                    if (tid == 0) bad = 1;
-                    break;
-                }
-                const double lkk = sqrt(d), ilkk = 1.0 / lkk;
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                if (cg == 0 && r >= k && r < kb) {
-                    const int at = (k0 + r) * D + k0 + k;
-                    S[at] = r == k ? lkk : S[at] * ilkk;
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                if (r > k && r < kb) {
-                    const double lrk = S[(k0 + r) * D + k0 + k];
+            const int r = tid & 15;                      // four copies of the block
+            double a[16], pv = 1.0;
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        const int j = 4 * cg + jj;
-                        if (j > k && j <= r) S[(k0 + r) * D + k0 + j] -= lrk * S[(k0 + j) * D + k0 + k];
-                    }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (int j = 0; j < 16; ++j) {
+                // (the last panel is completed with rows of the identity)
+                const double s = S[(r < kb ? k0 + r : k0) * DS + (k0 + j < M ? k0 + j : M - 1)];
+                a[j] = r >= kb || j >= kb ? (r == j ? 1.0 : 0.0) : s;
+            }
+            bool ok = true;                              // the same in every lane
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const double d = lane_value(a[k], k);
+                ok = ok && d > 0.0 && d < INFINITY;
+                const double il = rsqrt(d);
+                a[k] *= il;                              // row k: d / sqrt(d)
+                pv = r == k ? il : pv;
+#pragma unroll
+                for (int j = k + 1; j < 16; ++j) a[j] -= a[k] * lane_value(a[k], j);
+            }
+            if (!ok) bad = 1;
+            if (tid < kb) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    if (j <= r) S[(k0 + r) * DS + k0 + j] = a[j];
+                ipiv[k0 + r] = pv;
             }
         }
         __syncthreads();
         if (bad) break;
+        // the block's rows sit in the lanes of each working wave, so its entries
+        // are readlanes, not loads
         const int b0 = k0 + kb;
-        if (tid < kb) ipiv[k0 + tid] = 1.0 / S[(k0 + tid) * D + k0 + tid];
-        __syncthreads();
-        for (int i = b0 + tid; i < M; i += SOLVE_THREADS) {
-            double x[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) x[q] = q < kb ? S[i * D + k0 + q] : 0.0;
+        const int i = b0 + tid;
+        if (b0 + wave * WAVE <= M) {
+            const int is = i <= M ? i : M;
+            const int fr = k0 + ((lane & 15) < kb ? (lane & 15) : 0);
+            double x[16], f[16];
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
-                if (q < kb) {
-                    double v = x[q];
-#pragma unroll
-                    for (int pp = 0; pp < q; ++pp) v -= x[pp] * S[(k0 + q) * D + k0 + pp];
-                    x[q] = v * ipiv[k0 + q];
-                }
+                const int col = k0 + q < M ? k0 + q : M - 1;   // (columns past the last are not kept)
+                x[q] = S[is * DS + col];
+                f[q] = S[fr * DS + col];
             }
+            const double pl = ipiv[fr];
 #pragma unroll
-            for (int q = 0; q < 16; ++q)
-                if (q < kb) S[i * D + k0 + q] = x[q];
+            for (int q = 0; q < 16; ++q) {
+                x[q] *= lane_value(pl, q);
+#pragma unroll
+                for (int u = q + 1; u < 16; ++u) x[u] -= x[q] * lane_value(f[q], u);
+            }
+            if (i <= M) {
+#pragma unroll
+                for (int q = 0; q < 16; ++q)
+                    if (q < kb) S[i * DS + k0 + q] = x[q];
+            }
         }
+        if (b0 >= M) break;
         __syncthreads();
-        for (int i = b0 + ty; i < M; i += 16) {
-            double li[16];
+        // rank-16 update, one 16 x 16 tile of the trailing triangle per wave
+        // and turn: four products of the FP64 matrix cores, whose operands
+        // (lane l: row l % 16, column l / 16) are 8 loads a tile and lane
+        // instead of 32 an entry
+        const int nt = (M - b0 + 16) / 16;   // rows b0 ... M
+        const int cl = lane & 15, rl = lane >> 4;
+        for (int u = wave; u < nt * (nt + 1) / 2; u += SOLVE_THREADS / WAVE) {
+            int ti = 0, rem = u;
+            while (rem > ti) rem -= ++ti;
+            const int r0 = b0 + 16 * ti, c0 = b0 + 16 * rem;
+            const int ra = r0 + cl <= M ? r0 + cl : M, rb = c0 + cl <= M ? c0 + cl : M;
+            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int q = 0; q < 16; ++q) li[q] = q < kb ? S[i * D + k0 + q] : 0.0;
-            for (int j = b0 + tx; j <= i; j += 16) {
-                double v = 0.0;
+            for (int s = 0; s < 16; s += 4)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(S[ra * DS + k0 + s + rl], S[rb * DS + k0 + s + rl], acc,
+                                                           0, 0, 0);
 #pragma unroll
-                for (int q = 0; q < 16; ++q) v += q < kb ? li[q] * S[j * D + k0 + q] : 0.0;
-                S[i * D + j] -= v;
+            for (int e = 0; e < 4; ++e) {
+                const int row = r0 + rl + 4 * e, col = c0 + cl;
+                if (row <= M && col <= row && col < M) S[row * DS + col] -= acc[e];
             }
         }
         __syncthreads();
@@ -368,50 +412,42 @@ __global__ __launch_bounds__(SOLVE_THREADS) void solve_kernel(int M, const doubl
         if (loss && tid == 0) *loss = NAN;
         return;
     }
-    // a mirrored copy of the factor's columns in the upper triangle
-    // (S[j][i] = S[i][j], i > j), so both sweeps read rows; ipiv holds 1 / L_kk
-    for (int i = ty; i < M; i += 16)
-        for (int j = tx; j < i; j += 16) S[j * D + i] = S[i * D + j];
-    __syncthreads();
+    // back substitution L^T w = u: w_j = u_j / L_jj, u_i -= L_ji w_j for i < j
     if (tid < WAVE) {
         const int l = tid;
         const bool in0 = l < M, in1 = l + WAVE < M;
-        double r0 = in0 ? S[l * D + M] : 0.0;
-        double r1 = in1 ? S[(l + WAVE) * D + M] : 0.0;
-        // L u = r: u_j = r_j / L_jj, r_i -= L_ij u_j (L_ij mirrored at S[j][i]);
-        // row j + 1 and its pivot are read while step j runs
-        double a0 = in0 ? S[l] : 0.0, a1 = in1 ? S[l + WAVE] : 0.0, pj = ipiv[0];
-        for (int j = 0; j < M; ++j) {
-            const int jn = j + 1 < M ? j + 1 : j;
-            const double n0 = in0 ? S[jn * D + l] : 0.0, n1 = in1 ? S[jn * D + l + WAVE] : 0.0, pn = ipiv[jn];
-            const double uj = lane_value(j < WAVE ? r0 : r1, j & (WAVE - 1)) * pj;
-            if (l == (j & (WAVE - 1))) {
-                if (j < WAVE) r0 = uj;
-                else r1 = uj;
+        const int l0 = in0 ? l : 0, l1 = in1 ? l + WAVE : 0;
+        double r0 = S[M * DS + l0], r1 = S[M * DS + l1];
+        constexpr int AHEAD = 8;
+        double a0[AHEAD], a1[AHEAD], pj[AHEAD];
+        auto rows = [&](int j) {                         // rows j, j - 1, ...
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q) {
+                const int jq = j - q > 0 ? j - q : 0;
+                a0[q] = S[jq * DS + l0];
+                a1[q] = S[jq * DS + l1];
+                pj[q] = ipiv[jq];
             }
-            if (l > j && in0) r0 -= a0 * uj;
-            if (l + WAVE > j && in1) r1 -= a1 * uj;
-            a0 = n0;
-            a1 = n1;
-            pj = pn;
-        }
-        // L^T w = u: w_j = u_j / L_jj, u_i -= L_ji w_j for i < j
-        a0 = in0 ? S[(M - 1) * D + l] : 0.0;
-        a1 = in1 ? S[(M - 1) * D + l + WAVE] : 0.0;
-        pj = ipiv[M - 1];
-        for (int j = M - 1; j >= 0; --j) {
-            const int jn = j > 0 ? j - 1 : 0;
-            const double n0 = in0 ? S[jn * D + l] : 0.0, n1 = in1 ? S[jn * D + l + WAVE] : 0.0, pn = ipiv[jn];
-            const double wj = lane_value(j < WAVE ? r0 : r1, j & (WAVE - 1)) * pj;
-            if (l == (j & (WAVE - 1))) {
-                if (j < WAVE) r0 = wj;
-                else r1 = wj;
+        };
+        rows(M - 1);
+        for (int jb = M - 1; jb >= 0; jb -= AHEAD) {
+            double b0[AHEAD], b1[AHEAD], pb[AHEAD];
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q) {
+                b0[q] = a0[q];
+                b1[q] = a1[q];
+                pb[q] = pj[q];
             }
-            if (l < j) r0 -= a0 * wj;
-            if (l + WAVE < j) r1 -= a1 * wj;
-            a0 = n0;
-            a1 = n1;
-            pj = pn;
+            rows(jb - AHEAD);
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q) {
+                const int j = jb - q;
+                // (j < 0 changes no row)
+                const double wj = lane_value(j < WAVE ? r0 : r1, j & (WAVE - 1)) * pb[q];
+                const double d0 = r0 - b0[q] * wj, d1 = r1 - b1[q] * wj;
+                r0 = l == j ? wj : l < j ? d0 : r0;
+                r1 = l + WAVE == j ? wj : l + WAVE < j ? d1 : r1;
+            }
         }
         if (in0) {
             cv[l] = r0 * sc[l];
@@ -424,20 +460,34 @@ __global__ __launch_bounds__(SOLVE_THREADS) void solve_kernel(int M, const doubl
     }
     if (!loss) return;
     __syncthreads();
-    // objective from the unmodified Gram blocks, reloaded into LDS
-#pragma unroll 4
-    for (int e = tid; e < D * D; e += SOLVE_THREADS) S[e] = Z[e];
-    __syncthreads();
-    double* part = sc;   // M values; the scales are no longer needed
-    for (int i = tid; i < M; i += SOLVE_THREADS) {
-        double q = 0.0;
-        for (int j = 0; j < M; ++j) q += S[i * D + j] * cv[j];
-        part[i] = cv[i] * (q - 2.0 * S[i * D + M] + gamma * cv[i]);
+    // objective from the unmodified Gram blocks: the residual form
+    // sum_i c_i ((Z c)_i - 2 Z_ib + gamma c_i) + Z_bb.  Z goes back to LDS and
+    // four lanes share a row of Z c.
+    if (zc < M) {
+#pragma unroll
+        for (int q = 0; q < SOLVE_Z; ++q) {
+            const int i = zr + q * SOLVE_ROWS;
+            if (i <= M) S[i * DS + zc] = z[q];
+        }
     }
     __syncthreads();
+    double part = 0.0;
+    {
+        const int i = tid >> 2, l = tid & 3;
+        double q = 0.0;
+        if (i < M)
+            for (int j = l; j < M; j += 4) q += S[i * DS + j] * cv[j];
+#pragma unroll
+        for (int o = 1; o < 4; o <<= 1) q += __shfl_xor(q, o);
+        if (i < M && l == 0) part = cv[i] * (q - 2.0 * S[M * DS + i] + gamma * cv[i]);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
+    if ((tid & (WAVE - 1)) == 0) red[tid / WAVE] = part;
+    __syncthreads();
     if (tid == 0) {
-        double s = S[M * D + M];
-        for (int i = 0; i < M; ++i) s += part[i];
+        double s = zbb;
+        for (int w = 0; w < SOLVE_THREADS / WAVE; ++w) s += red[w];
         *loss = s;
     }
 }
@@ -512,8 +562,8 @@ int pod_fit_solve(pod_handle* h, int M, const double* Z, double gamma, double* c
     using namespace pod;
     if (!h || M < 1 || !Z || !c) return POD_EINVAL;
     if (!std::isfinite(gamma) || gamma < 0.0) return POD_EINVAL;
-    const size_t lds = sizeof(double) * (static_cast<size_t>(M + 1) * (M + 1) + 3 * static_cast<size_t>(M));
-    if (M > 2 * WAVE) return POD_ENOTSUP;   // two right-hand-side rows per lane
+    const size_t lds = sizeof(double) * (static_cast<size_t>(M + 1) * ((M + 1) | 1) + 3 * static_cast<size_t>(M));
+    if (M > SOLVE_MAX_M) return POD_ENOTSUP;
     if (lds > h->lds_max) return POD_ENOTSUP;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(solve_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                             static_cast<int>(lds)) != hipSuccess)

@@ -171,3 +171,22 @@ def test_fit_from_assembled_matrix(setup, c_tol):
     assert loss.item() <= 1e-10 * float(bb @ bb)
     if c_tol is not None:
         assert np.abs(got - c_true).max() <= c_tol * np.abs(c_true).max()
+
+
+@pytest.mark.parametrize("M", [2, 15, 16, 17, 31, 48, 63, 64, 65, 95, 112, 128])
+def test_solve_panel_edges(M):
+    """Sizes around the 16-column panels, the 64 rows a lane holds of the back
+    substitution, and the largest size; a diagonally scaled random problem
+    (condition below 1e3), so the normal equations agree with the oracle's
+    orthogonal solve to 1e3 x 128 x 2^-52 = 3e-11 at worst."""
+    say(f"[gpu] fit solve panel edge M={M}")
+    m = _h()
+    G, E, dG, F = _problem(100 + M, 40, 20 * M + 7, M)
+    A, b = fo.design_matrix(G, dG, E, F, 10.0, 1.0)
+    c = torch.empty(M, dtype=torch.float64, device="cuda")
+    loss = torch.empty(1, dtype=torch.float64, device="cuda")
+    pod.pod_fit_solve(m.h, M, _dev(fo.gram(A, b)), 1e-3, c, loss)
+    pod.pod_check(m.h)
+    ref = fo.ridge_solve(A, b, 1e-3)
+    assert np.abs(c.cpu().numpy() - ref).max() <= 1e-10 * np.abs(ref).max()
+    assert abs(loss.item() - fo.objective(A, b, ref, 1e-3)) <= 1e-9 * float(b @ b)
