@@ -74,32 +74,32 @@ def lib():
     L.pod_compute_basis.argtypes = [P(PodParamsC), _dp, _dp]
     L.pod_num_descriptors.argtypes = [_vp, P(i), P(i)]
     L.pod_get_basis.argtypes = [_vp, _dp, _dp]
-    L.pod_descriptors.argtypes = [_vp, i, i, _vp, _dp, _vp, _vp, _vp, _vp]
-    L.pod_energy_forces.argtypes = [_vp, i, i, _vp, _dp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
-    L.pod_energy_forces_noalloc.argtypes = [_vp, i, i, _vp, _dp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
+    L.pod_descriptors.argtypes = [_vp, i, i, _vp, _vp, _vp, _vp, _vp, _vp]
+    L.pod_energy_forces.argtypes = [_vp, i, i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
+    L.pod_energy_forces_noalloc.argtypes = [_vp, i, i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
     L.pod_neighbor_reverse.argtypes = [_vp, i, i, _vp, _vp, _vp, _vp]
     L.pod_batch_assemble.argtypes = [_vp, i, i, i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, P(PodTuneC)]
     lg, f = ctypes.c_long, ctypes.c_float
-    L.pod_build_neighbors.argtypes = [_vp, i, _vp, _dp, ctypes.c_double, _vp, _vp, _vp, lg, P(lg)]
+    L.pod_build_neighbors.argtypes = [_vp, i, _vp, _vp, ctypes.c_double, _vp, _vp, _vp, lg, P(lg)]
     d = ctypes.c_double
     L.pod_fit_gram.argtypes = [_vp, i, i, _vp, _vp, d, lg, _vp, _vp, d, i, _vp]
     L.pod_fit_solve.argtypes = [_vp, i, _vp, d, _vp, _vp]
-    L.pod_opod_descriptors.argtypes = [_vp, i, i, _vp, _dp, _vp, _vp, _vp, _vp]
-    L.pod_md_verlet.argtypes = [_vp, i, i, _vp, _vp, _vp, _dp, _vp, _vp, _vp, _vp, _vp, d, d, i, _vp, _vp, _vp, _vp]
+    L.pod_opod_descriptors.argtypes = [_vp, i, i, _vp, _vp, _vp, _vp, _vp, _vp]
+    L.pod_md_verlet.argtypes = [_vp, i, i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, d, d, i, _vp, _vp, _vp, _vp]
     L.pod_md_max_displacement.argtypes = [_vp, i, _vp, _vp, _vp]
-    L.pod_opod_energy_forces.argtypes = [_vp, i, i, _vp, _dp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
+    L.pod_opod_energy_forces.argtypes = [_vp, i, i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
     L.pod_mlp_num_params.argtypes = [i]
     L.pod_mlp_forward.argtypes = [_vp, i, i, _vp, lg, _vp, _vp, _vp, _vp, _vp]
     L.pod_mlp_train_step.argtypes = [_vp, i, i, _vp, lg, _vp, _vp, _vp, _vp, _vp, _vp, i, f, f, f, f, _vp]
-    L.pod_energy_forces_surrogate.argtypes = [_vp, i, i, _vp, _dp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
+    L.pod_energy_forces_surrogate.argtypes = [_vp, i, i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
                                               _vp, _vp, _vp]
     L.pod_five_body_count.argtypes = [i, P(i)]
-    L.pod_five_body_descriptors.argtypes = [_vp, i, i, _vp, _dp, _vp, _vp, _vp, i, i, _vp]
-    L.pod_five_body_energy_forces.argtypes = [_vp, i, i, _vp, _dp, _vp, _vp, _vp, _vp, i, i, _vp, _vp, _vp]
+    L.pod_five_body_descriptors.argtypes = [_vp, i, i, _vp, _vp, _vp, _vp, _vp, i, i, _vp]
+    L.pod_five_body_energy_forces.argtypes = [_vp, i, i, _vp, _vp, _vp, _vp, _vp, _vp, i, i, _vp, _vp, _vp]
     L.pod_acsf_create.argtypes = [_vp, i, _dp, i, _dp, i, _dp, P(_vp)]
     L.pod_acsf_num_functions.argtypes = [_vp, P(i), P(i)]
-    L.pod_acsf_descriptors.argtypes = [_vp, _vp, i, i, _vp, _dp, _vp, _vp, _vp, _vp]
-    L.pod_acsf_forces.argtypes = [_vp, _vp, i, i, _vp, _dp, _vp, _vp, _vp, _vp, _vp, lg, _vp, _vp]
+    L.pod_acsf_descriptors.argtypes = [_vp, _vp, i, i, _vp, _vp, _vp, _vp, _vp, _vp]
+    L.pod_acsf_forces.argtypes = [_vp, _vp, i, i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, lg, _vp, _vp]
     L.pod_acsf_free.argtypes = [_vp]
     L.pod_acsf_free.restype = None
     L.pod_check.argtypes = [_vp]
@@ -141,14 +141,17 @@ def _ok(rc, where):
 
 
 def _ptr(t):
-    """Device pointer of a torch tensor (None -> NULL)."""
+    """Device address of a torch tensor (None -> NULL), for a void pointer argument.
+
+    A plain integer: the call converts it, and a ctypes object per argument is
+    a third of the time that marshalling takes."""
     if t is None:
         return None
     if not t.is_cuda:
         raise ValueError("expected a device tensor")
     if not t.is_contiguous():
         raise ValueError("expected a contiguous tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _ptr_at(t, elem_offset):
@@ -157,14 +160,17 @@ def _ptr_at(t, elem_offset):
         raise ValueError("expected a contiguous device tensor")
     if not 0 <= elem_offset < max(t.numel(), 1):
         raise ValueError("offset outside the tensor")
-    return ctypes.c_void_p(t.data_ptr() + int(elem_offset) * t.element_size())
+    return t.data_ptr() + int(elem_offset) * t.element_size()
 
 
 def _cell_ptr(cell):
+    """(array, address) of nine contiguous doubles; the caller keeps the array."""
     if cell is None:
         return None, None
-    arr = np.ascontiguousarray(np.asarray(cell, dtype=np.float64).reshape(9))
-    return arr, arr.ctypes.data_as(_dp)
+    arr = np.ascontiguousarray(cell, dtype=np.float64)
+    if arr.size != 9:
+        raise ValueError(f"cannot reshape array of size {arr.size} into shape (9,)")
+    return arr, arr.__array_interface__["data"][0]
 
 
 @dataclass
