@@ -121,6 +121,19 @@ int mlp_forward_launch(pod_handle* h, int n, int n_in, const void* X, long ldx, 
 namespace net {
 struct Packed;
 }
+// One velocity Verlet step inside the energy path's finalize kernel.
+struct MdStep {
+    void* x;                  // positions, velocities, list positions (or null): handle dtype
+    void* v;
+    const void* xr;
+    double hka, dt, half_m_over_acc;
+    double* ke;               // kinetic-energy partials, one per 8 atoms
+    double* disp;             // running displacement maxima, one per 8 atoms (or null)
+    int drift;                // also the next step's half kick and drift
+};
+// Energy and forces (force gather: rev and F given) and the step, on the handle's stream.
+int energy_forces_md(pod_handle* h, int N, int P, const double* cell, const int* offsets, const int* nbr_j,
+                     const int* shift, const int* rev, const void* c, double* E, void* F, const MdStep& md);
 // The network weights packed for the per-atom energy kernel (one small
 // kernel on the handle's stream); out: device memory of sizeof(net::Packed).
 int mlp_pack_launch(pod_handle* h, int n_in, const float* theta, const float* mu, const float* isg,

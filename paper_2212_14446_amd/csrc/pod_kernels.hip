@@ -856,8 +856,12 @@ struct FinArgs {
     int* err;
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void finalize_kernel(FinArgs<T> f) {
+// MD: the gather's blocks also take their atoms through the closing half kick
+// of a velocity Verlet step and, with drift, the opening half kick and drift
+// of the next: every atom's force is final in its lanes, and nothing of the
+// evaluation reads the positions any more.
+template <typename T, bool MD>
+__device__ __forceinline__ void finalize_body(const FinArgs<T>& f, const MdStep& md) {
     const int col = blockIdx.x;
     if (col >= f.ncol) {
         const int fb = f.rev ? xcd_block(col - f.ncol, (f.N + 7) / 8) : col - f.ncol;
@@ -892,6 +896,51 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs<T> f) {
                 f.F[3 * a + 0] = static_cast<T>(f0);
                 f.F[3 * a + 1] = static_cast<T>(f1);
                 f.F[3 * a + 2] = static_cast<T>(f2);
+            }
+            if constexpr (MD) {
+                __shared__ double ske[8], sdp[8];
+                T* x = static_cast<T*>(md.x);
+                T* v = static_cast<T*>(md.v);
+                const T* xr = static_cast<const T*>(md.xr);
+                const bool on = a < f.N && s0 < 3;   // lane s0: component s0
+                double ke = 0.0, d2 = 0.0;
+                if (on) {
+                    const long k = 3L * a + s0;
+                    const double fc = static_cast<double>(static_cast<T>(s0 == 0 ? f0 : s0 == 1 ? f1 : f2));
+                    const double vs = static_cast<double>(static_cast<T>(static_cast<double>(v[k]) + md.hka * fc));
+                    ke = vs * vs;
+                    if (md.drift) {
+                        const double vh = vs + md.hka * fc;
+                        v[k] = static_cast<T>(vh);
+                        const T xn = static_cast<T>(static_cast<double>(x[k]) + md.dt * vh);
+                        x[k] = xn;
+                        if (xr) {
+                            const double dd = static_cast<double>(xn) - static_cast<double>(xr[k]);
+                            d2 = dd * dd;
+                        }
+                    } else {
+                        v[k] = static_cast<T>(vs);
+                    }
+                }
+                const double k1 = __shfl(ke, 1, 32), k2 = __shfl(ke, 2, 32);
+                const double d1 = __shfl(d2, 1, 32), d2b = __shfl(d2, 2, 32);
+                if (s0 == 0) {
+                    ske[threadIdx.x / 32] = ke + k1 + k2;
+                    sdp[threadIdx.x / 32] = sqrt(d2 + d1 + d2b);
+                }
+                __syncthreads();
+                if (threadIdx.x == 0) {
+                    double s = 0.0, mx = 0.0;
+                    for (int q = 0; q < 8; ++q) {
+                        s += ske[q];
+                        mx = (sdp[q] > mx || sdp[q] != sdp[q]) ? sdp[q] : mx;   // a NaN displacement wins
+                    }
+                    md.ke[fb] = s * md.half_m_over_acc;
+                    if (md.drift && md.disp) {
+                        const double o = md.disp[fb];
+                        md.disp[fb] = (mx > o || mx != mx) ? mx : o;
+                    }
+                }
             }
         } else {
             const long i = static_cast<long>(fb) * 256 + threadIdx.x;
@@ -933,6 +982,22 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs<T> f) {
         else if (col < 10) W[col - 1] = v;
         else G[col - 10] = v;
     }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void finalize_kernel(FinArgs<T> f) {
+    finalize_body<T, false>(f, MdStep{});
+}
+template <typename T>
+__global__ __launch_bounds__(256) void finalize_md_kernel(FinArgs<T> f, MdStep md) {
+    finalize_body<T, true>(f, md);
+}
+
+template <typename T>
+hipError_t launch_finalize(const FinArgs<T>& f, int nblk, const MdStep* md, hipStream_t st) {
+    if (md) hipLaunchKernelGGL((finalize_md_kernel<T>), dim3(nblk), dim3(256), 0, st, f, *md);
+    else hipLaunchKernelGGL((finalize_kernel<T>), dim3(nblk), dim3(256), 0, st, f);
+    return hipGetLastError();
 }
 
 // Reverse-pair index: for pair p = (i -> j, n) find the first q = (j -> i,
@@ -1179,7 +1244,7 @@ template <typename T, int MODE = 1>
 int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, const void* pos, const double* cell,
                       const int* offsets, const int* nbr_j, const int* shift, const int* rev, const void* c,
                       void* E_atom, double* E, void* F, double* W, double* G,
-                      const net::Packed* netw = nullptr, int n_net = 0) {
+                      const net::Packed* netw = nullptr, int n_net = 0, const MdStep* md = nullptr) {
     KArgs<T> a;
     int rc = fill_args<T>(h, a, N, P, pos, cell, offsets, nbr_j, shift);
     if (rc != POD_OK) return rc;
@@ -1229,9 +1294,9 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
         const int nfb = gather ? (N + 7) / 8 : static_cast<int>((fa.n3 + 255) / 256);
         if (E || W || G || nfb > 0) {
             timing_begin(h, 0);
-            hipLaunchKernelGGL((finalize_kernel<T>), dim3(ncol + nfb), dim3(256), 0, h->stream, fa);
+            const hipError_t ef = launch_finalize<T>(fa, ncol + nfb, md, h->stream);
             timing_end(h, 0);
-            if (hipGetLastError() != hipSuccess) return POD_EHIP;
+            if (ef != hipSuccess) return POD_EHIP;
         }
         return POD_OK;
     }
@@ -1275,9 +1340,9 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
     const int nfb = gather ? (N + 7) / 8 : static_cast<int>((fa.n3 + 255) / 256);
     if (E || W || G || nfb > 0) {
         timing_begin(h, 0);
-        hipLaunchKernelGGL((finalize_kernel<T>), dim3(ncol + nfb), dim3(256), 0, h->stream, fa);
+        const hipError_t ef = launch_finalize<T>(fa, ncol + nfb, md, h->stream);
         timing_end(h, 0);
-        if (hipGetLastError() != hipSuccess) return POD_EHIP;
+        if (ef != hipSuccess) return POD_EHIP;
     }
     return POD_OK;
 }
@@ -1286,7 +1351,7 @@ template <typename T, int MODE = 1>
 int energy_forces_impl(pod_handle* h, int N, int P, const void* pos, const double* cell, const int* offsets,
                        const int* nbr_j, const int* shift, const int* rev, const void* c, void* E_atom, double* E,
                        void* F, double* W, double* G, const net::Packed* netw = nullptr,
-                       int n_net = 0) {
+                       int n_net = 0, const MdStep* md = nullptr) {
     const bool back = (F != nullptr) || (W != nullptr);
     const bool gather = rev != nullptr && F != nullptr;
     const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, MODE == 2);
@@ -1295,7 +1360,7 @@ int energy_forces_impl(pod_handle* h, int N, int P, const void* pos, const doubl
     rc = ensure_force_acc(h, N);
     if (rc != POD_OK) return rc;
     rc = energy_forces_run<T, MODE>(h, static_cast<char*>(h->d_scratch), h->d_facc, N, P, pos, cell, offsets, nbr_j,
-                                    shift, rev, c, E_atom, E, F, W, G, netw, n_net);
+                                    shift, rev, c, E_atom, E, F, W, G, netw, n_net, md);
     if (rc == POD_EHIP && back && !gather) h->facc_dirty = 1;
     return rc;
 }
@@ -1374,6 +1439,15 @@ bool bad_common(pod_handle* h, int N, int P, const void* pos, const int* offsets
 }
 
 }  // namespace
+
+int energy_forces_md(pod_handle* h, int N, int P, const double* cell, const int* offsets, const int* nbr_j,
+                     const int* shift, const int* rev, const void* c, double* E, void* F, const MdStep& md) {
+    if (h->dtype == POD_F64)
+        return energy_forces_impl<double>(h, N, P, md.x, cell, offsets, nbr_j, shift, rev, c, nullptr, E, F, nullptr,
+                                          nullptr, nullptr, 0, &md);
+    return energy_forces_impl<float>(h, N, P, md.x, cell, offsets, nbr_j, shift, rev, c, nullptr, E, F, nullptr,
+                                     nullptr, nullptr, 0, &md);
+}
 
 int resolve_static_scratch(int dev) {
     if (dev < 0 || dev >= MAX_DEVICES) return POD_EHIP;

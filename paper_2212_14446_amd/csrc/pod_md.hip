@@ -21,6 +21,12 @@ constexpr double ACC = 1.602176634e-19 / 1e-10 / 1.66053906660e-27 * 1e-20;
 constexpr int MD_THREADS = 256;
 constexpr int MD_BLOCKS = 512;   // grid-stride kernels; partial sums per block
 constexpr int KE_RING = 64;      // steps of kinetic-energy partials folded together
+// Up to this many atoms the kicks and the drift run inside the finalize kernel
+// of the force evaluation: one launch a step less, at the price of one partial
+// sum per 8 atoms, which one workgroup per step folds.  40 steps with their list
+// rebuilds, separate / inside: 128 atoms 1,594 / 1,473 us, 2,000 2,617 / 2,466,
+// 15,840 3,917 / 3,814 (FP64) and 3,228 / 3,147 (FP32), 59,582 6,281 / 6,290 (FP32).
+constexpr int MD_FUSE_N = 32768;
 
 // v += dt/2 a F, x += dt v, one atom per thread; with a reference, the
 // block's running maximum of |x - x_ref| over the steps in its own slot of
@@ -206,10 +212,13 @@ int verlet_impl(pod_handle* h, int N, int P, void* pos, void* vel, void* F, cons
                 const int* nbr_j, const int* shift, const int* rev, const void* c, double mass, double dt, int nsteps,
                 double* E_pot, double* E_kin, const void* pos_ref, double* max_disp) {
     const int nb1 = md_blocks(N);
-    int rc = ensure_mscratch(h, sizeof(double) * (KE_RING + 1) * MD_BLOCKS);
+    const bool fuse = rev && N > 0 && N <= MD_FUSE_N;
+    const int nbk = fuse ? (N + 7) / 8 : nb1;                // kinetic-energy partials a step
+    const int slots = nbk > MD_BLOCKS ? nbk : MD_BLOCKS;
+    int rc = ensure_mscratch(h, sizeof(double) * (KE_RING + 1) * slots);
     if (rc != POD_OK) return rc;
     double* partd = static_cast<double*>(h->d_mscratch);   // running displacement maxima
-    double* ring = partd + MD_BLOCKS;                       // kinetic-energy partials, KE_RING steps
+    double* ring = partd + slots;                           // kinetic-energy partials, KE_RING steps
     const double hka = 0.5 * dt * ACC / mass;
     const double half_m_over_acc = 0.5 * mass / ACC;
     T* x = static_cast<T*>(pos);
@@ -218,7 +227,7 @@ int verlet_impl(pod_handle* h, int N, int P, void* pos, void* vel, void* F, cons
     const T* xr = max_disp ? static_cast<const T*>(pos_ref) : nullptr;
     if (max_disp) {
         hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(MD_THREADS), 0, h->stream, max_disp, 1);
-        hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(MD_THREADS), 0, h->stream, partd, MD_BLOCKS);
+        hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(MD_THREADS), 0, h->stream, partd, slots);
     }
     // step s: half kick + drift, forces, half kick; the closing half kick of
     // step s and the opening half kick and drift of step s + 1 share one
@@ -227,11 +236,20 @@ int verlet_impl(pod_handle* h, int N, int P, void* pos, void* vel, void* F, cons
         hipLaunchKernelGGL((kick_drift_kernel<T>), dim3(nb1), dim3(MD_THREADS), 0, h->stream, N, x, v, f, xr, hka, dt,
                            xr ? partd : nullptr);
     for (int s = 0; s < nsteps; ++s) {
-        rc = pod_energy_forces(h, N, P, pos, cell, offsets, nbr_j, shift, rev, c, nullptr, E_pot ? E_pot + s : nullptr,
-                               F, nullptr, nullptr);
+        double* ke = ring + static_cast<long>(s % KE_RING) * slots;
+        if (fuse) {
+            MdStep md;
+            md.x = pos; md.v = vel; md.xr = xr;
+            md.hka = hka; md.dt = dt; md.half_m_over_acc = half_m_over_acc;
+            md.ke = ke; md.disp = xr ? partd : nullptr;
+            md.drift = s + 1 < nsteps;
+            rc = energy_forces_md(h, N, P, cell, offsets, nbr_j, shift, rev, c, E_pot ? E_pot + s : nullptr, F, md);
+        } else {
+            rc = pod_energy_forces(h, N, P, pos, cell, offsets, nbr_j, shift, rev, c, nullptr,
+                                   E_pot ? E_pot + s : nullptr, F, nullptr, nullptr);
+        }
         if (rc != POD_OK) return rc;
-        double* ke = ring + static_cast<long>(s % KE_RING) * MD_BLOCKS;
-        if (N > 0) {
+        if (N > 0 && !fuse) {
             if (s + 1 < nsteps)
                 hipLaunchKernelGGL((kick_atoms_kernel<T, true>), dim3(nb1), dim3(MD_THREADS), 0, h->stream, N, x, v, f,
                                    xr, hka, dt, half_m_over_acc, ke, xr ? partd : nullptr);
@@ -242,12 +260,12 @@ int verlet_impl(pod_handle* h, int N, int P, void* pos, void* vel, void* F, cons
         // kinetic energies of up to KE_RING steps in one launch, one block per step
         if (E_kin && (s % KE_RING == KE_RING - 1 || s == nsteps - 1)) {
             const int cnt = s % KE_RING + 1;
-            hipLaunchKernelGGL(fold_kernel, dim3(cnt), dim3(MD_THREADS), 0, h->stream, ring, N > 0 ? nb1 : 0, 0,
-                               E_kin + (s + 1 - cnt), static_cast<long>(MD_BLOCKS));
+            hipLaunchKernelGGL(fold_kernel, dim3(cnt), dim3(MD_THREADS), 0, h->stream, ring, N > 0 ? nbk : 0, 0,
+                               E_kin + (s + 1 - cnt), static_cast<long>(slots));
         }
     }
     if (max_disp && N > 0)
-        hipLaunchKernelGGL(fold_kernel, dim3(1), dim3(MD_THREADS), 0, h->stream, partd, nb1, 2, max_disp, 0L);
+        hipLaunchKernelGGL(fold_kernel, dim3(1), dim3(MD_THREADS), 0, h->stream, partd, slots, 2, max_disp, 0L);
     return hipGetLastError() == hipSuccess ? POD_OK : POD_EHIP;
 }
 

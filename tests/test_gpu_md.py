@@ -102,3 +102,43 @@ def test_max_displacement_and_errors():
         with pytest.raises(pod.PodError) as e:
             pod.pod_md_verlet(*args, mass, dt, 1, **extra)
         assert pod.ERRORS[e.value.code] == "POD_EINVAL"
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,nsteps", [(2, 1), (2, 3), (3, 66), (6, 5)])
+def test_step_with_and_without_reverse_index(dtype, n, nsteps):
+    """With a reverse index the kicks and the drift run inside the force
+    gather; without one they are kernels of their own.  The two force sums
+    differ in order only (32 terms at most here: 32 x 2^-53 relative in FP64
+    of forces that move a step by 1e-3 of a unit), so trajectories agree to
+    1e-11 (f64) and 2e-5 (f32, forces rounded to 2^-24 of a few eV/A)."""
+    say(f"[gpu] md with/without reverse index n={n} steps={nsteps} {dtype}")
+    import paper_2212_14446_amd.workloads as wl
+    setup = wl.PodSetup(0.5, 5.0, 8, 4, 4, 4, 3, 3)
+    m = pod.PodModel(pod.setup_from_workload(setup), dtype)
+    rng = np.random.default_rng(17)
+    base = np.stack(np.meshgrid(*[np.arange(n)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    pos = 3.3 * np.concatenate([base, base + 0.5]) + rng.normal(scale=0.05, size=(2 * n ** 3, 3))
+    cell = 3.3 * n * np.eye(3)
+    N = len(pos)
+    x0 = torch.as_tensor(pos, dtype=m.torch_dtype, device="cuda")
+    v0 = torch.as_tensor(rng.normal(scale=1e-3, size=(N, 3)), dtype=m.torch_dtype, device="cuda")
+    c = torch.as_tensor(rng.normal(scale=1e-3, size=m.M), dtype=m.torch_dtype, device="cuda")
+    nb = pod.DeviceNeighbors.build(m, x0, cell, rlist=5.4)
+    nb.build_reverse(m)
+    res = []
+    for rev in (nb.rev, None):
+        x, v = x0.clone(), v0.clone()
+        F = m.energy_forces(x, cell, nb, c)["F"]
+        ep = torch.empty(nsteps, dtype=torch.float64, device="cuda")
+        ek = torch.empty_like(ep)
+        disp = torch.empty(1, dtype=torch.float64, device="cuda")
+        pod.pod_md_verlet(m.h, N, nb.P, x, v, F, cell, nb.offsets, nb.nbr_j, nb.shift, rev, c, 180.9, 1.0, nsteps,
+                          ep, ek, x0, disp)
+        m.check()
+        res.append([t.double().cpu().numpy() for t in (x, v, F, ep, ek, disp)])
+    tol = 1e-11 if dtype == "f64" else 2e-5
+    for a, b in zip(*res):
+        assert np.abs(a - b).max() <= tol * max(np.abs(b).max(), 1e-30)
+    x = res[0][0]
+    assert res[0][5][0] >= np.linalg.norm(x - x0.double().cpu().numpy(), axis=1).max() * (1 - 1e-12)
