@@ -159,14 +159,16 @@ int pod_build_neighbors(pod_handle* h, int N, const void* pos, const double* cel
                         int* offsets, int* nbr_j, int* shift, long capacity, long* n_pairs);
 
 /* Linear POD energy and its derivatives (eqs. (57a), (58a), (26c), (24c)).
- * Three kernels on the handle's stream: the per-atom kernel (atomic basis,
+ * Kernels on the handle's stream: the per-atom kernel (atomic basis,
  * contractions, energy, adjoint rows dE_i/dB_i), the pair kernel (g_p =
- * dE_i/dr_ij of every pair, virial) and the finalize kernel (totals, forces).
+ * dE_i/dr_ij of every pair, virial) and the finalize kernel (totals, forces);
+ * for small systems one workgroup per atom does the work of the first two in
+ * one launch, for wide-degree models a record kernel and a per-atom kernel do.
  *   rev    : reverse-pair index from pod_neighbor_reverse, or NULL.  With it,
  *            forces are gathered per atom, F_n = sum_{p in N(n)} (g_p - g_rev(p))
  *            with g_p = dE_i/dr_ij, in a fixed order (bitwise reproducible):
- *            each g_p is stored at its own slot p and at slot rev(p), so atom
- *            n's gather reads its own list range.  rev must be the list's
+ *            each g_p is stored once, at slot p, and the gather reads it again
+ *            through rev.  rev must be the list's
  *            reverse index (a pair without a reverse latches POD_ENEIGH).
  *            Without rev, forces are accumulated with FP64 atomics.
  *   c      : M coefficients (device, handle dtype)
@@ -484,8 +486,9 @@ void pod_acsf_free(pod_acsf* a);
  * of their kernels (n = 0 switches recording off).  pod_get_kernel_time waits
  * for the stream and returns the summed elapsed time (ms) and the number of
  * recorded launches of one kernel -- kind 1: the per-atom kernel (radial
- * basis, atomic basis, contractions, energy, adjoint rows) and the
- * batched-assembly kernel; kind 4: the pair-gradient kernel of the energy
+ * basis, atomic basis, contractions, energy, adjoint rows; for small systems
+ * and wide-degree models the kernels that also form the pair gradients) and the
+ * batched-assembly kernels; kind 4: the pair-gradient kernel of the energy
  * calls (per-pair gradients, own-atom sums, virial); kind 0: the finalize
  * kernel (totals E, W, G and the force gather or copy-out); kind 2: the
  * network kernels (for the surrogate: its weight packing; its network runs
