@@ -1184,7 +1184,8 @@ int descriptors_impl(pod_handle* h, int N, int P, const void* pos, const double*
         if (rc2 != POD_OK) return rc2;
         w.rec = static_cast<T*>(h->d_scratch);
         timing_begin(h, 1);
-        const hipError_t e = launch_wide<T>(w, 0, h->std_ok != 0, wide_blocks(N), h->stream);
+        const hipError_t e = launch_wide<T>(w, 0, h->std_ok != 0, h->K4 > 0 ? wide_desc_blocks(N) : wide_blocks(N),
+                                             h->stream);
         timing_end(h, 1);
         return e == hipSuccess ? POD_OK : POD_EHIP;
     }

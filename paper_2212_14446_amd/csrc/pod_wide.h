@@ -54,10 +54,10 @@ struct WideLds {
 
 __host__ __device__ constexpr size_t wide_align(size_t b) { return (b + 15) & ~size_t(15); }
 
-// Row stride of the basis and adjoint rows: 16 modulo 32, so that two rows'
+// Row stride of the basis and adjoint rows: 17 modulo 32, so that two rows'
 // runs of 16 doubles (the operand of a matrix instruction) fall into
-// different LDS banks.
-__host__ __device__ constexpr int wide_row(int NA) { return (NA + 15) / 32 * 32 + 16; }
+// different LDS banks, and one entry of all rows (4-body terms) as well.
+__host__ __device__ constexpr int wide_row(int NA) { return (NA + 15) / 32 * 32 + 17; }
 // Stride of a pair's power table: three components with a leading zero
 // (u^-1), made odd.
 __host__ __device__ constexpr int wide_pw(int PA) { return (3 * (PA + 2)) | 1; }
@@ -69,28 +69,45 @@ __host__ __device__ constexpr int wide_tab_ints() {
     return 3 * n_partitions(POD_MAX_P4) + 4 * D4Table<POD_MAX_P4>::NT + n_mono(POD_MAX_P4) + 1 + POD_MAX_P4 + 1;
 }
 
-__host__ __device__ constexpr WideLds wide_lds(int K, int PA, int M, bool four, int tsize) {
+// Of the packed tables, what the descriptors alone need: without the occurrences.
+__host__ __device__ constexpr int wide_desc_ints() {
+    return 3 * n_partitions(POD_MAX_P4) + D4Table<POD_MAX_P4>::NT;
+}
+
+// Descriptors alone (energy false) take no coefficients, radial derivatives and
+// gradient sums, and keep the parts of the degree sums where the power table
+// was: K = 12, P3 = 10, P4 = 6 in FP64 74 -> 50 KB, three workgroups per
+// compute unit instead of two (15,840 atoms 330 -> 266 us without 4-body terms).
+__host__ __device__ constexpr WideLds wide_lds(int K, int PA, int M, bool four, int tsize, bool energy) {
     const size_t ts = static_cast<size_t>(tsize);
     const size_t NA = static_cast<size_t>(n_mono(PA));
     WideLds L{};
     L.coef = 0;
-    L.code = wide_align(L.coef + static_cast<size_t>(M) * ts);
+    L.code = wide_align(L.coef + (energy ? static_cast<size_t>(M) * ts : 0));
     L.fact = wide_align(L.code + NA * sizeof(int));
     L.inv = wide_align(L.fact + NA * sizeof(float));
     L.tab = wide_align(L.inv + (POD_MAX_P + 1) * ts);
-    L.b = wide_align(L.tab + (four ? static_cast<size_t>(wide_tab_ints()) * sizeof(int) : 0));
+    L.b = wide_align(L.tab + (four ? static_cast<size_t>(energy ? wide_tab_ints() : wide_desc_ints()) * sizeof(int) : 0));
     L.s = wide_align(L.b + static_cast<size_t>(K) * wide_row(static_cast<int>(NA)) * ts);
     L.part = wide_align(L.s + static_cast<size_t>(K) * (PA + 1) * ts);
-    L.b0 = wide_align(L.part + static_cast<size_t>(K) * WIDE_PARTS * ts);
+    const size_t part = wide_align(static_cast<size_t>(K) * WIDE_PARTS * ts);
+    const size_t pw = wide_align(static_cast<size_t>(WIDE_CHUNK) * wide_pw(PA) * ts);
+    L.b0 = L.part + (energy ? part : part > pw ? part : pw);
     L.r = wide_align(L.b0 + static_cast<size_t>(K) * ts);
-    L.pw = wide_align(L.r + static_cast<size_t>(WIDE_CHUNK) * (4 + 2 * K) * ts);
-    L.g = wide_align(L.pw + static_cast<size_t>(WIDE_CHUNK) * wide_pw(PA) * ts);
-    L.red = wide_align(L.g + 4 * static_cast<size_t>(WIDE_CHUNK) * 4 * ts);
+    const size_t r = wide_align(L.r + static_cast<size_t>(WIDE_CHUNK) * (4 + (energy ? 2 : 1) * K) * ts);
+    L.pw = energy ? r : L.part;
+    L.g = energy ? L.pw + pw : r;
+    L.red = wide_align(L.g + (energy ? 4 * static_cast<size_t>(WIDE_CHUNK) * 4 * ts : 0));
     L.total = wide_align(L.red + 16 * sizeof(double));
     return L;
 }
 
 inline int wide_blocks(int N) { return N < WIDE_MAX_BLOCKS ? N : WIDE_MAX_BLOCKS; }
+// Descriptors leave no partials per workgroup, so with 4-body terms, whose long
+// term lists dwarf a workgroup's start, four times as many even out the last
+// turn of the chip (K = 12, P4 = 6 1,178 -> 1,132 us FP64, 861 -> 779 FP32;
+// without 4-body terms 266 -> 290 us, so those keep wide_blocks).
+inline int wide_desc_blocks(int N) { return N < 4 * WIDE_MAX_BLOCKS ? N : 4 * WIDE_MAX_BLOCKS; }
 
 // The energy path of a model with K radial functions and angular degree PA
 // runs here when either exceeds what the register-resident kernels hold.

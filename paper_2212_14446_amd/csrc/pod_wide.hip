@@ -59,7 +59,7 @@ constexpr int WT = WIDE_THREADS;
 constexpr int CH = WIDE_CHUNK;
 constexpr int NWV = WT / WAVE;
 constexpr int NA_MAX = n_mono(POD_MAX_P);                   // 286
-constexpr int MPT = (NA_MAX + WT - 1) / WT;                 // monomials per thread in the adjoint
+constexpr int APT = (POD_MAX_K * n_mono(POD_MAX_P4) + WT - 1) / WT;   // 4-body adjoint entries per thread
 constexpr int TPW = ((NA_MAX + 15) / 16 + NWV - 1) / NWV;   // 16-monomial tiles per wavefront
 constexpr int KSTEP = (POD_MAX_K + 3) / 4;                  // matrix steps over the radial index
 constexpr int DPT = 2;                                      // descriptor columns per thread
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(WT) void wide_pair_kernel(WideArgs<T> g) {
 
 // VL: the virial's sums in LDS (one column per thread of the gradient's end)
 // instead of 18 registers of every thread.
-template <typename T, int MODE, bool VL>
+template <typename T, int MODE, bool VL, bool FOUR>
 __device__ __forceinline__ void wide_body(const WideArgs<T>& g) {
     extern __shared__ __align__(16) unsigned char smem[];
     const ParamsT<T>& prm = g.prm;
@@ -247,8 +247,8 @@ __device__ __forceinline__ void wide_body(const WideArgs<T>& g) {
     const int NR = wide_row(NA);       // row stride of the basis rows
     const int PA1 = PA + 1, PA2 = PA + 2, PST = wide_pw(PA);
     const int nt = (NA + 15) / 16;     // 16-monomial tiles
-    const bool four = prm.K4 > 0;
-    const WideLds L = wide_lds(K, PA, M, four, static_cast<int>(sizeof(T)));
+    const bool four = MODE == 1 ? FOUR : prm.K4 > 0;   // 4-body terms
+    const WideLds L = wide_lds(K, PA, M, four, static_cast<int>(sizeof(T)), MODE == 1);
     T* sC = reinterpret_cast<T*>(smem + L.coef);
     int* sCode = reinterpret_cast<int*>(smem + L.code);
     int* sTab = reinterpret_cast<int*>(smem + L.tab);
@@ -280,7 +280,7 @@ __device__ __forceinline__ void wide_body(const WideArgs<T>& g) {
     if (MODE == 1)
         for (int k = tid; k < M; k += WT) sC[k] = g.coef[k];
     if (four)
-        for (int k = tid; k < wide_tab_ints(); k += WT) sTab[k] = kWide.tab[k];
+        for (int k = tid; k < (MODE == 1 ? wide_tab_ints() : wide_desc_ints()); k += WT) sTab[k] = kWide.tab[k];
     __syncthreads();
 
     const int K2 = prm.K2, K3 = prm.K3, K4 = prm.K4, P3 = prm.P3, P4 = prm.P4, KA = prm.Ka4;
@@ -455,12 +455,21 @@ __device__ __forceinline__ void wide_body(const WideArgs<T>& g) {
                     T v0 = T(0), v1 = T(0);
                     const int t1 = sTab[T_TEND + p];
                     int t = sTab[T_TBEG + p];
-                    for (; t + 1 < t1; t += 2) {                                    // eq. (30a)
+                    // four terms' twelve loads in flight (two: K = 12, P4 = 6
+                    // FP64 1,132 us against 790, FP32 779 against 502)
+                    for (; t + 3 < t1; t += 4) {                                    // eq. (30a)
                         const int ta = sTab[T_TERM + t], tb = sTab[T_TERM + t + 1];
-                        v0 += T(ta >> 21) * Bk[ta & 127] * Bk[(ta >> 7) & 127] * Bk[(ta >> 14) & 127];
-                        v1 += T(tb >> 21) * Bk[tb & 127] * Bk[(tb >> 7) & 127] * Bk[(tb >> 14) & 127];
+                        const int tc = sTab[T_TERM + t + 2], td = sTab[T_TERM + t + 3];
+                        const T xa = Bk[ta & 127], ya = Bk[(ta >> 7) & 127], za = Bk[(ta >> 14) & 127];
+                        const T xb = Bk[tb & 127], yb = Bk[(tb >> 7) & 127], zb = Bk[(tb >> 14) & 127];
+                        const T xc = Bk[tc & 127], yc = Bk[(tc >> 7) & 127], zc = Bk[(tc >> 14) & 127];
+                        const T xd = Bk[td & 127], yd = Bk[(td >> 7) & 127], zd = Bk[(td >> 14) & 127];
+                        v0 += T(ta >> 21) * xa * ya * za;
+                        v1 += T(tb >> 21) * xb * yb * zb;
+                        v0 += T(tc >> 21) * xc * yc * zc;
+                        v1 += T(td >> 21) * xd * yd * zd;
                     }
-                    if (t < t1) {
+                    for (; t < t1; ++t) {
                         const int ta = sTab[T_TERM + t];
                         v0 += T(ta >> 21) * Bk[ta & 127] * Bk[(ta >> 7) & 127] * Bk[(ta >> 14) & 127];
                     }
@@ -480,20 +489,51 @@ __device__ __forceinline__ void wide_body(const WideArgs<T>& g) {
             if (!g.want_back) __syncthreads();
         }
         if (MODE == 1 && g.want_back) {
-            // ---- 3. adjoint dE_i/dB_{k n}, one radial index at a time: the
-            // contractions are diagonal in k, so row k of the adjoint needs
-            // only row k of the basis and overwrites it in place
-            const T* cf = sC;
-#pragma unroll 1
-            for (int k = 0; four && k < K; ++k) {
-                T* Bk = sB + k * NR;
-                const T B0 = Bk[0];
-                T ab[MPT];
+            // ---- 3. adjoint dE_i/dB_{k n}, in place.  The 4-body part of an entry
+            // reads other entries of its row, all with n < NA4: those parts are
+            // formed first, for all rows at once, and kept over a barrier.
+            // Neighbouring lanes take the radial indices of one monomial: they
+            // walk the same occurrences and read rows an odd stride apart.  (One
+            // row at a time left two thirds of the threads idle: 15,840 atoms,
+            // K = 12, P4 = 6 FP64 5,100 -> 2,228 us per call.)
+            if (four) {
+                const T* cf = sC;
+                const int n4 = NA < NA4 ? NA : NA4;
+                T a4[APT];
 #pragma unroll
-                for (int j = 0; j < MPT; ++j) {
-                    ab[j] = T(0);
-                    const int nn = tid + j * WT;
-                    if (nn >= NA) continue;
+                for (int j = 0; j < APT; ++j) {
+                    a4[j] = T(0);
+                    const int t = tid + j * WT;
+                    if (t >= K * n4) continue;
+                    const int nn = t / K, k = t - nn * K;
+                    if (k >= K4) continue;
+                    const T* Bk = sB + k * NR;
+                    const T* c4 = cf + off4 + k * KA;
+                    // occurrences are sorted by p: stop at the first p of a
+                    // higher degree than the model's; four at a time
+                    const int o0 = sTab[T_OBEG + nn], o1 = sTab[T_OBEG + nn + 1];
+                    T v4 = T(0);
+                    int o = o0;
+                    for (; o + 3 < o1; o += 4) {                                      // eq. (30a)
+                        const int oa = sTab[T_OCC + o], ob = sTab[T_OCC + o + 1];
+                        const int oc = sTab[T_OCC + o + 2], od = sTab[T_OCC + o + 3];
+                        if ((od & 31) >= KA) break;
+                        v4 += c4[oa & 31] * T(oa >> 19) * Bk[(oa >> 5) & 127] * Bk[(oa >> 12) & 127];
+                        v4 += c4[ob & 31] * T(ob >> 19) * Bk[(ob >> 5) & 127] * Bk[(ob >> 12) & 127];
+                        v4 += c4[oc & 31] * T(oc >> 19) * Bk[(oc >> 5) & 127] * Bk[(oc >> 12) & 127];
+                        v4 += c4[od & 31] * T(od >> 19) * Bk[(od >> 5) & 127] * Bk[(od >> 12) & 127];
+                    }
+                    for (; o < o1; ++o) {
+                        const int oa = sTab[T_OCC + o];
+                        if ((oa & 31) >= KA) break;
+                        v4 += c4[oa & 31] * T(oa >> 19) * Bk[(oa >> 5) & 127] * Bk[(oa >> 12) & 127];
+                    }
+                    a4[j] = v4;
+                }
+                __syncthreads();   // every product of basis entries is formed
+                // the parts that need the entry itself only
+                auto entry = [&](int k, int nn, T v4) {
+                    T* Bk = sB + k * NR;
                     const int cd = sCode[nn];
                     const int dg = (cd >> 12) & 15;
                     const T mult = T(cd >> 16);
@@ -505,38 +545,18 @@ __device__ __forceinline__ void wide_body(const WideArgs<T>& g) {
                         const T* c4 = cf + off4 + k * KA;
                         if (nn == 0)
                             for (int a = 0; a <= P4; ++a) v += c4[p_a00(sTab, a)] * sS[k * PA1 + a];   // eq. (27a)
-                        if (dg <= P4) v += c4[p_a00(sTab, dg)] * B0 * T(2) * mult * Bn;
-                        if (nn < NA4) {
-                            // occurrences are sorted by p: stop at the first p of a
-                            // higher degree than the model's; four at a time
-                            const int o0 = sTab[T_OBEG + nn], o1 = sTab[T_OBEG + nn + 1];
-                            T v4 = T(0);
-                            int o = o0;
-                            for (; o + 3 < o1; o += 4) {                                      // eq. (30a)
-                                const int oa = sTab[T_OCC + o], ob = sTab[T_OCC + o + 1];
-                                const int oc = sTab[T_OCC + o + 2], od = sTab[T_OCC + o + 3];
-                                if ((od & 31) >= KA) break;
-                                v4 += c4[oa & 31] * T(oa >> 19) * Bk[(oa >> 5) & 127] * Bk[(oa >> 12) & 127];
-                                v4 += c4[ob & 31] * T(ob >> 19) * Bk[(ob >> 5) & 127] * Bk[(ob >> 12) & 127];
-                                v4 += c4[oc & 31] * T(oc >> 19) * Bk[(oc >> 5) & 127] * Bk[(oc >> 12) & 127];
-                                v4 += c4[od & 31] * T(od >> 19) * Bk[(od >> 5) & 127] * Bk[(od >> 12) & 127];
-                            }
-                            for (; o < o1; ++o) {
-                                const int oa = sTab[T_OCC + o];
-                                if ((oa & 31) >= KA) break;
-                                v4 += c4[oa & 31] * T(oa >> 19) * Bk[(oa >> 5) & 127] * Bk[(oa >> 12) & 127];
-                            }
-                            v += v4;
-                        }
+                        if (dg <= P4) v += c4[p_a00(sTab, dg)] * sB0[k] * T(2) * mult * Bn;
                     }
-                    ab[j] = v;
-                }
-                __syncthreads();   // every read of row k is done
+                    Bk[nn] = (v + v4) * T(sFact[nn]);
+                };
 #pragma unroll
-                for (int j = 0; j < MPT; ++j)
-                    if (tid + j * WT < NA) Bk[tid + j * WT] = ab[j] * T(sFact[tid + j * WT]);
+                for (int j = 0; j < APT; ++j) {
+                    const int t = tid + j * WT;
+                    if (t < K * n4) entry(t - t / K * K, t / K, a4[j]);
+                }
+                for (int t = tid; t < K * (NA - n4); t += WT) entry(t - t / K * K, n4 + t / K, T(0));
+                __syncthreads();
             }
-            if (four) __syncthreads();
             const T* sA = sB;   // adjoint rows [K][NR], times a! b! c!
 
             // ---- 4. pair gradients, eq. (24c)
@@ -690,17 +710,25 @@ __device__ __forceinline__ void wide_body(const WideArgs<T>& g) {
 // Wavefronts per SIMD.  The energy kernel of a model whose LDS lets three
 // workgroups share a compute unit is held to three (K = 10, P3 = 8 FP64: 526 ->
 // 451 us, K = 12, P3 = 10 FP32: 473 -> 406 us); with K = 12, P3 = 10 in FP64 only
-// two fit, and the same kernel took 793 us against 753.
+// two fit, and the same kernel took 793 us against 753 when it was held to three.
 constexpr int wide_waves(int mode) { return mode == 0 ? 4 : 2; }
 
 template <typename T, int MODE>
 __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(wide_waves(MODE)))) void wide_kernel(WideArgs<T> g) {
-    wide_body<T, MODE, false>(g);
+    wide_body<T, MODE, false, false>(g);
 }
 
 template <typename T>
 __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(3))) void wide_kernel_occ3(WideArgs<T> g) {
-    wide_body<T, 1, true>(g);
+    wide_body<T, 1, true, false>(g);
+}
+
+// With 4-body terms: an instance of its own, whose adjoint needs registers that
+// the others are faster without (K = 12, P3 = 10 FP32: 518 against 399 us); in
+// FP32 at three wavefronts per SIMD (K = 12, P4 = 6: 2,506 -> 1,489 us).
+template <typename T>
+__global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 2))) void wide_kernel_four(WideArgs<T> g) {
+    wide_body<T, 1, sizeof(T) == 4, true>(g);
 }
 
 template <typename T, int MODE>
@@ -713,9 +741,11 @@ hipError_t launch_mode(const WideArgs<T>& a, bool fast, int nblk, hipStream_t st
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const size_t lds = wide_lds(a.prm.K, a.prm.PA, a.prm.M, a.prm.K4 > 0, static_cast<int>(sizeof(T))).total;
+    const size_t lds = wide_lds(a.prm.K, a.prm.PA, a.prm.M, a.prm.K4 > 0, static_cast<int>(sizeof(T)), MODE == 1).total;
     constexpr size_t STATIC = WIDE_PARTS * sizeof(int) + 9 * CH * sizeof(double);
-    if (MODE == 1 && lds + STATIC <= 163840 / 3)
+    if (MODE == 1 && a.prm.K4 > 0)
+        hipLaunchKernelGGL((wide_kernel_four<T>), dim3(nblk), dim3(WT), lds, st, a);
+    else if (MODE == 1 && lds + STATIC <= 163840 / 3)
         hipLaunchKernelGGL((wide_kernel_occ3<T>), dim3(nblk), dim3(WT), lds, st, a);
     else
         hipLaunchKernelGGL((wide_kernel<T, MODE>), dim3(nblk), dim3(WT), lds, st, a);

@@ -185,3 +185,21 @@ def test_wide_refused_where_the_register_kernels_are_required():
     with pytest.raises(pod.PodError) as e:
         pod.batch_assemble(m, pod.DeviceBatch.from_batch(b))
     assert pod.ERRORS[e.value.code] == "POD_ENOTSUP"
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("L,K2,K3,K4,P3,P4", [(12, 9, 2, 3, 3, 3), (12, 9, 9, 9, 1, 6), (12, 2, 3, 10, 7, 1),
+                                              (14, 12, 12, 12, 7, 6)])
+def test_wide_four_body_entries(box49, dtype, L, K2, K3, K4, P3, P4):
+    """4-body adjoint entries of all rows at once: rows shorter and longer than
+    the 84 monomials of degree 6, fewer 4-body than radial indices and the most
+    of both; the tolerances are the main parity tests'."""
+    pos, cell = box49
+    s = wl.PodSetup(0.5, 5.0, L, K2, K3, K4, P3, P4)
+    nl = wl.neighbor_list(pos, cell, s.rcut)
+    c = wl.coefficients(s.M, seed=500 + L + K2 + 3 * K3 + 5 * K4 + 7 * P3 + 11 * P4)
+    say(f"[gpu] wide 4-body {dtype} K={K2},{K3},{K4} P={P3},{P4}")
+    errs = _compare(Case(pos, cell, nl, s, c, f"wide4_{dtype}_K{K2},{K3},{K4}_P{P3},{P4}"), dtype)
+    for k, v in errs.items():
+        tol = TOL64 if dtype == "f64" else {"E": 2e-5, "E_atom": 2e-5, "D": 1e-3}.get(k, 1e-4)
+        assert v < tol, (k, v)
