@@ -285,13 +285,15 @@ __global__ __launch_bounds__(SOLVE_THREADS) void solve_kernel(int M, const doubl
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1), wave = tid / WAVE;
     if (tid == 0) bad = 0;
-    // columns 0 ... M - 1 of all rows (row M is the right-hand side)
+    // columns 0 ... M - 1 of rows 0 ... M - 1 and, as row M, the right-hand side:
+    // the interface puts it in column M; what the last row of Z holds left of
+    // the corner is not read
     const int zr = tid / SOLVE_MAX_M, zc = tid % SOLVE_MAX_M;
     double z[SOLVE_Z];
 #pragma unroll
     for (int q = 0; q < SOLVE_Z; ++q) {
         const int i = zr + q * SOLVE_ROWS;
-        z[q] = i <= M && zc < M ? Z[i * D + zc] : 0.0;
+        z[q] = i <= M && zc < M ? Z[i < M ? i * D + zc : zc * D + M] : 0.0;
     }
     const double zbb = Z[M * D + M];
     for (int i = tid; i < M; i += SOLVE_THREADS) sc[i] = Z[i * D + i];
