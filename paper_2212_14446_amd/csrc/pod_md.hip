@@ -27,6 +27,11 @@ constexpr int KE_RING = 64;      // steps of kinetic-energy partials folded toge
 // rebuilds, separate / inside: 128 atoms 1,594 / 1,473 us, 2,000 2,617 / 2,466,
 // 15,840 3,917 / 3,814 (FP64) and 3,228 / 3,147 (FP32), 59,582 6,281 / 6,290 (FP32).
 constexpr int MD_FUSE_N = 32768;
+// The scratch of every call of this file is one size (2.1 MB): a step captured in a
+// graph keeps its buffer when a larger system follows on the same handle.
+constexpr int MD_SLOTS = MD_FUSE_N / 8;
+constexpr size_t MD_SCRATCH = sizeof(double) * (KE_RING + 1) * MD_SLOTS;
+static_assert(MD_SLOTS >= MD_BLOCKS, "a slot per block of the separate kernels");
 
 // v += dt/2 a F, x += dt v, one atom per thread; with a reference, the
 // block's running maximum of |x - x_ref| over the steps in its own slot of
@@ -215,10 +220,10 @@ int verlet_impl(pod_handle* h, int N, int P, void* pos, void* vel, void* F, cons
     const bool fuse = rev && N > 0 && N <= MD_FUSE_N;
     const int nbk = fuse ? (N + 7) / 8 : nb1;                // kinetic-energy partials a step
     const int slots = nbk > MD_BLOCKS ? nbk : MD_BLOCKS;
-    int rc = ensure_mscratch(h, sizeof(double) * (KE_RING + 1) * slots);
+    int rc = ensure_mscratch(h, MD_SCRATCH);
     if (rc != POD_OK) return rc;
     double* partd = static_cast<double*>(h->d_mscratch);   // running displacement maxima
-    double* ring = partd + slots;                           // kinetic-energy partials, KE_RING steps
+    double* ring = partd + MD_SLOTS;                         // kinetic-energy partials, KE_RING steps
     const double hka = 0.5 * dt * ACC / mass;
     const double half_m_over_acc = 0.5 * mass / ACC;
     T* x = static_cast<T*>(pos);
@@ -293,7 +298,7 @@ int pod_md_max_displacement(pod_handle* h, int N, const void* pos, const void* p
     using namespace pod;
     if (!h || N < 0 || !out || (N > 0 && (!pos || !pos_ref))) return POD_EINVAL;
     const int nb = md_blocks(N);
-    const int rc = ensure_mscratch(h, sizeof(double) * MD_BLOCKS);
+    const int rc = ensure_mscratch(h, MD_SCRATCH);
     if (rc != POD_OK) return rc;
     double* part = static_cast<double*>(h->d_mscratch);
     if (N > 0) {
