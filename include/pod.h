@@ -225,7 +225,9 @@ int pod_energy_forces_noalloc(pod_handle* h, int N, int P, const void* pos, cons
  * device-to-host copy of both), so the call returns after the plan, with the
  * kernels queued on the handle's stream.  A cell with more atoms than the
  * LDS accumulator holds (the limit depends on M and the tune) gives
- * POD_ENOTSUP.  Scratch grows in the handle (POD_ENOMEM on failure). */
+ * POD_ENOTSUP.  Scratch grows in the handle: the pair records and basis rows
+ * of the cells, in rounds of up to 2 GB of them; where the device has less, in
+ * smaller rounds (POD_ENOMEM when it has not enough for the largest cell). */
 typedef struct pod_tune {
     int cw;       /* most descriptor columns per dG/dR chunk (0 = library's
                      choice; lowered until the cell's LDS accumulator fits the

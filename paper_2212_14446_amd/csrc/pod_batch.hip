@@ -3,7 +3,7 @@
 // global descriptors G = sum_i D_i of each cell and their derivatives
 // dG/dr_n (Sec. II.G, eqs. (26c), (24c), product rule for the 2- and 4-body
 // terms), in FP64.  Three kernels over the cells in order of decreasing pair
-// count (batches beyond 2 GB of scratch in several rounds of them):
+// count (batches beyond 2 GB of scratch, or what the device has, in several rounds of them):
 //   1. pair records: (rhat, 1/r) per pair and, per radial index, (R_m, R'_m),
 //      in slot-major order (see BArgs);
 //   2. forward: lanes (atom, m) accumulate the atomic-basis rows (eq. (24b)),
@@ -631,37 +631,28 @@ int pod_batch_assemble(pod_handle* h, int n_cfg, int N, int P, const int* cfg_at
     BatchPlan plan;
     int rc = plan_batch(n_cfg, N, P, coff.data(), off.data(), h->M, h->lds_max, tune, &plan);
     if (rc != POD_OK) return rc;
-    // The records and basis rows of a launch's cells live in the handle's
-    // scratch; batches that need more than SCRATCH_CAP run in several launches
-    // of consecutive cells (at least one cell each).
+    // The records and basis rows of a round's cells live in the handle's
+    // scratch; batches that need more than SCRATCH_CAP run in several rounds of
+    // consecutive cells, and where the device does not have that much, in
+    // rounds of half the size, and so on down to one cell a round.
     constexpr size_t SCRATCH_CAP = size_t(2) << 30;
     const int NB = n_mono(h->PA) + h->PA + 1;
     const size_t per_ent = (4 + 2 * static_cast<size_t>(h->K)) * sizeof(double) + sizeof(int);
     const size_t per_atom = static_cast<size_t>(h->K) * NB * sizeof(double);
-    std::vector<int> first{0};   // first cell of every launch, then n_cfg
-    std::vector<long> ebase(n_cfg), n_ent;   // first entry of every cell within its launch; entries per launch
-    size_t most = 0, bytes = 0;
-    long ent = 0;
-    for (int c = 0; c < n_cfg; ++c) {
-        int longest = 0;
-        for (int i = coff[c]; i < coff[c + 1]; ++i) longest = std::max(longest, off[i + 1] - off[i]);
-        const long e = static_cast<long>(longest) * (coff[c + 1] - coff[c]);
-        const size_t need = e * per_ent + static_cast<size_t>(coff[c + 1] - coff[c]) * per_atom;
-        if (c > first.back() && bytes + need > SCRATCH_CAP) {
-            first.push_back(c);
-            n_ent.push_back(ent);
-            most = std::max(most, bytes);
-            bytes = 0;
-            ent = 0;
-        }
-        ebase[c] = ent;
-        ent += e;
-        bytes += need;
-    }
-    first.push_back(n_cfg);
-    n_ent.push_back(ent);
-    most = std::max(most, bytes);
-    // processing order (decreasing pair count) of each launch's cells
+    const size_t order_bytes = ((sizeof(int) * n_cfg + 255) / 256) * 256;
+    const size_t base_bytes = ((sizeof(long) * n_cfg + 255) / 256) * 256;
+    BatchRounds rounds;
+    rc = fit_rounds(
+        n_cfg, coff.data(), off.data(), per_ent, per_atom, SCRATCH_CAP,
+        [&](size_t bytes) {
+            const int r = ensure_scratch(h, order_bytes + base_bytes + bytes + 256);
+            if (r == POD_ENOMEM) (void)hipGetLastError();   // answered here, not by the next launch
+            return r;
+        },
+        &rounds);
+    if (rc != POD_OK) return rc;
+    const std::vector<int>& first = rounds.first;
+    // processing order (decreasing pair count) of each round's cells
     std::vector<int> order(n_cfg);
     if (first.size() == 2) {
         order = plan.order;
@@ -670,14 +661,10 @@ int pod_batch_assemble(pod_handle* h, int n_cfg, int N, int P, const int* cfg_at
         for (int c : plan.order)
             order[at[std::upper_bound(first.begin(), first.end(), c) - first.begin() - 1]++] = c;
     }
-    const size_t order_bytes = ((sizeof(int) * n_cfg + 255) / 256) * 256;
-    const size_t base_bytes = ((sizeof(long) * n_cfg + 255) / 256) * 256;
-    rc = ensure_scratch(h, order_bytes + base_bytes + most + 256);
-    if (rc != POD_OK) return rc;
     int* d_order = static_cast<int*>(h->d_scratch);
     long* d_ebase = reinterpret_cast<long*>(static_cast<char*>(h->d_scratch) + order_bytes);
     if (hipMemcpyAsync(d_order, order.data(), sizeof(int) * n_cfg, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
-        hipMemcpyAsync(d_ebase, ebase.data(), sizeof(long) * n_cfg, hipMemcpyHostToDevice, h->stream) != hipSuccess)
+        hipMemcpyAsync(d_ebase, rounds.ebase.data(), sizeof(long) * n_cfg, hipMemcpyHostToDevice, h->stream) != hipSuccess)
         return POD_EHIP;
     BArgs a;
     a.prm = h->hp_d;
@@ -715,7 +702,7 @@ int pod_batch_assemble(pod_handle* h, int n_cfg, int N, int P, const int* cfg_at
         a.n_cell = c1 - c0;
         a.order = d_order + c0;
         a.a_base = coff[c0];
-        a.n_ent = n_ent[k];
+        a.n_ent = rounds.n_ent[k];
         a.n_at = coff[c1] - coff[c0];
         a.recU = reinterpret_cast<double*>(static_cast<char*>(h->d_scratch) + order_bytes + base_bytes);
         a.recR = a.recU + 4 * a.n_ent;

@@ -205,6 +205,35 @@ int open_geometry(const double* pos, int N, double rlist, NbGeom* g) {
     return POD_OK;
 }
 
+void plan_rounds(int n_cfg, const int* coff, const int* off, size_t per_ent, size_t per_atom, size_t cap,
+                 BatchRounds* r) {
+    r->first.assign(1, 0);
+    r->ebase.resize(n_cfg);
+    r->n_ent.clear();
+    r->bytes = 0;
+    size_t bytes = 0;
+    long ent = 0;
+    for (int c = 0; c < n_cfg; ++c) {
+        int longest = 0;
+        for (int i = coff[c]; i < coff[c + 1]; ++i) longest = std::max(longest, off[i + 1] - off[i]);
+        const long nc = coff[c + 1] - coff[c], e = longest * nc;
+        const size_t need = static_cast<size_t>(e) * per_ent + static_cast<size_t>(nc) * per_atom;
+        if (c > r->first.back() && bytes + need > cap) {
+            r->first.push_back(c);
+            r->n_ent.push_back(ent);
+            r->bytes = std::max(r->bytes, bytes);
+            bytes = 0;
+            ent = 0;
+        }
+        r->ebase[c] = ent;
+        ent += e;
+        bytes += need;
+    }
+    r->first.push_back(n_cfg);
+    r->n_ent.push_back(ent);
+    r->bytes = std::max(r->bytes, bytes);
+}
+
 int plan_batch(int n_cfg, int N, int P, const int* coff, const int* off, int M, size_t lds_max,
                const pod_tune* tune, BatchPlan* plan) {
     if (n_cfg < 1 || N < 0 || P < 0 || !coff || !off || !plan || M < 1) return POD_EINVAL;
