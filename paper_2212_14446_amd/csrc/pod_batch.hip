@@ -215,7 +215,7 @@ __device__ __forceinline__ void row_task(const int* __restrict__ recJ, const Row
         nA = U2[2 * a]; nB = U2[2 * a + 1]; nR = R2[a];
         nj = recJ[a];
     }
-    int e = a;
+    long e = a;
     for (int s = 1; s <= cnt; ++s) {
         const int jl = nj;
         const double ux = nA.x, uy = nA.y, uz = nB.x, Rr = nR.x * nB.y, dR = nR.y;
@@ -393,7 +393,7 @@ __global__ __launch_bounds__(BASIS_THREADS) void batch_basis_kernel(BArgs g) {
                 double Rm[GP];
 #pragma unroll
                 for (int s = 0; s < GP; ++s) {
-                    const int e = min(s0 + s, cnt - 1) * Nc + a;
+                    const long e = static_cast<long>(min(s0 + s, cnt - 1)) * Nc + a;
                     uA[s] = U2[2 * e]; uB[s] = U2[2 * e + 1];
                     Rm[s] = R2[e].x;
                 }
@@ -479,8 +479,8 @@ __global__ __launch_bounds__(deriv_threads(PA)) void batch_deriv_kernel(BArgs g)
     // run on one XCD (workgroup i runs on XCD i mod 8) and share its records in
     // that L2
     const int per_cell = K * g.nch;
-    const int n_item = (g.n_cell + 7) / 8 * 8 * per_cell;
-    for (int w = blockIdx.x; w < n_item; w += gridDim.x) {
+    const unsigned n_item = (g.n_cell + 7u) / 8 * 8 * per_cell;   // at most 2^20 cells x 8 x 31
+    for (unsigned w = blockIdx.x; w < n_item; w += gridDim.x) {
         const int rank = (w >> 3) / per_cell * 8 + (w & 7), im = (w >> 3) % per_cell;
         const int m = im / g.nch, ch = im - m * g.nch;
         if (rank >= g.n_cell) continue;
@@ -587,8 +587,11 @@ hipError_t launch_batch(const BArgs& a, bool fast, int nitem, int nth, size_t ld
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&batch_deriv_kernel<PA>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
         return hipErrorInvalidValue;
-    const int all = (a.n_cell + 7) / 8 * 8 * a.prm.K * a.nch;
-    if (nitem <= 0 || nitem > all) nitem = all;
+    // one workgroup per item, as far as a launch's 2^32 threads reach: the
+    // kernel's loop takes the rest
+    const long all = (a.n_cell + 7L) / 8 * 8 * a.prm.K * a.nch;
+    const int most = static_cast<int>(std::min(all, 1L << 22));
+    if (nitem <= 0 || nitem > most) nitem = most;
     if (nth <= 0) nth = deriv_threads(PA);
     if (nth > deriv_threads(PA)) nth = deriv_threads(PA);
     hipLaunchKernelGGL((batch_deriv_kernel<PA>), dim3(nitem), dim3(nth), lds, st, a);

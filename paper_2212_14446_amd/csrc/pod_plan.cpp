@@ -218,7 +218,7 @@ void plan_rounds(int n_cfg, const int* coff, const int* off, size_t per_ent, siz
         for (int i = coff[c]; i < coff[c + 1]; ++i) longest = std::max(longest, off[i + 1] - off[i]);
         const long nc = coff[c + 1] - coff[c], e = longest * nc;
         const size_t need = static_cast<size_t>(e) * per_ent + static_cast<size_t>(nc) * per_atom;
-        if (c > r->first.back() && bytes + need > cap) {
+        if (c > r->first.back() && (bytes + need > cap || c - r->first.back() >= BATCH_MAX_CELLS)) {
             r->first.push_back(c);
             r->n_ent.push_back(ent);
             r->bytes = std::max(r->bytes, bytes);

@@ -71,9 +71,12 @@ constexpr int BATCH_MAX_THREADS = 512;
 // Rounds of pod_batch_assemble: the pair records and basis rows of one
 // round's cells are in scratch at a time.  Cells are taken in order; a round
 // ends before the cell that would take its scratch beyond cap bytes (a cell
-// that needs more by itself has a round of its own).  A cell has longest list
+// that needs more by itself has a round of its own) or after BATCH_MAX_CELLS
+// cells (a launch has at most 2^32 threads).  A cell has longest list
 // x atoms record entries of per_ent bytes (lists padded to the cell's longest)
 // and per_atom bytes for every atom.
+constexpr int BATCH_MAX_CELLS = 1 << 20;
+
 struct BatchRounds {
     std::vector<int> first;      // first cell of every round, then n_cfg
     std::vector<long> ebase;     // first record entry of every cell within its round

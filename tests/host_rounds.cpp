@@ -96,6 +96,11 @@ int main() {
         if (rc == POD_OK) CHECK(r.bytes <= have);
         consistent(s, r, size_t(-1));
     }
+    // a round has at most BATCH_MAX_CELLS cells, whatever they need
+    Cells empty;
+    empty.coff.assign(2 * pod::BATCH_MAX_CELLS + 4, 0);
+    pod::plan_rounds(empty.n(), empty.coff.data(), empty.off.data(), ENT, ATOM, all, &r);
+    CHECK((r.first == std::vector<int>{0, pod::BATCH_MAX_CELLS, 2 * pod::BATCH_MAX_CELLS, empty.n()}) && r.bytes == 0);
     // another answer ends the search
     int calls = 0;
     CHECK(pod::fit_rounds(s.n(), s.coff.data(), s.off.data(), ENT, ATOM, all,

@@ -32,3 +32,26 @@ def test_several_rounds():
     for k in ("D", "G", "dGdR"):
         ref, got = one[k], out[k].view(copies, *one[k].shape)
         assert float((got - ref).abs().max()) <= 1e-12 * float(ref.abs().max()), k
+
+
+def test_more_cells_than_a_launch_takes():
+    """2^20 + 3 equal dimers, one column per chunk: more cells than a round has
+    and more items than a launch has workgroups.  Every cell as the first."""
+    s = wl.PodSetup(0.5, 5.0, 6, 4, 4, 0, 3, 0)
+    m = pod.PodModel(pod.setup_from_workload(s), "f64")
+    n = 2 ** 20 + 3
+    say(f"[gpu] batch of {n} dimers")
+    x = np.array([[0.1, 0.2, 0.3], [1.1, 2.0, 2.3]])
+    cell = 40.0 * np.eye(3).reshape(1, 9)
+
+    def batch(k):
+        one = np.arange(2 * k).reshape(k, 2)
+        return pod.DeviceBatch(2 * np.arange(k + 1), np.tile(x, (k, 1)), np.tile(cell, (k, 1)), np.arange(2 * k + 1),
+                               one[:, ::-1].ravel(), np.zeros(2 * k, np.int32))
+
+    ref = pod.batch_assemble(m, batch(1), tune=(1, 0, 0))
+    out = pod.batch_assemble(m, batch(n), tune=(1, 0, 0))
+    for k in ("D", "G", "dGdR"):
+        assert float(ref[k].abs().max()) > 0.0
+        got = out[k].view(n, *ref[k].shape)
+        assert float((got - ref[k]).abs().max()) <= 1e-13 * float(ref[k].abs().max()), k
