@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "pod.h"
@@ -31,6 +32,7 @@ constexpr int NB_THREADS = 256;
 // 1,024,000 atoms (FP32) 2.48 / 2.56 / 2.77 ms (one thread per atom: 303, 324
 // us and 4.25 ms), so one width serves the whole range.
 constexpr int NB_LANES = 16;
+constexpr int NB_SLICE = 1 << 27;      // atoms per launch of the search, which has at most 2^32 threads
 constexpr int NB_MAX_WRAP = 1 << 20;   // |lattice vectors| between an atom and its home cell
 
 __device__ __forceinline__ int floor_div(int a, int b) {
@@ -110,7 +112,7 @@ __global__ __launch_bounds__(NB_THREADS) void order_kernel(int N, const int* __r
 // candidate loads.
 // (Count and fill pass for 15,840 atoms: 95 + 118 us before.)
 template <bool FILL, int G>
-__global__ __launch_bounds__(NB_THREADS) void search_kernel(int N, NbGeom g, const int* __restrict__ key,
+__global__ __launch_bounds__(NB_THREADS) void search_kernel(int i0, int N, NbGeom g, const int* __restrict__ key,
                                                             const int* __restrict__ sidx,
                                                             const int* __restrict__ start, const int* __restrict__ end,
                                                             const double* __restrict__ wpos,
@@ -121,7 +123,7 @@ __global__ __launch_bounds__(NB_THREADS) void search_kernel(int N, NbGeom g, con
     static_assert(G == 8 || G == 16 || G == 32, "lanes per atom");
     constexpr unsigned GM = G == 32 ? 0xFFFFFFFFu : (1u << G) - 1u;
     const int lane = threadIdx.x % WAVE, sub = threadIdx.x % G;
-    const int i = blockIdx.x * (NB_THREADS / G) + static_cast<int>(threadIdx.x) / G;
+    const int i = i0 + static_cast<int>(blockIdx.x) * (NB_THREADS / G) + static_cast<int>(threadIdx.x) / G;
     if (i >= N) return;   // whole groups
     const int b = key[i];
     const int ci[3] = {b % g.nb[0], (b / g.nb[0]) % g.nb[1], b / (g.nb[0] * g.nb[1])};
@@ -315,9 +317,16 @@ int pod_build_neighbors(pod_handle* h, int N, const void* pos, const double* cel
     hipLaunchKernelGGL(fill_int_kernel, gbins, tb, 0, h->stream, start, nbins, 0);
     hipLaunchKernelGGL(fill_int_kernel, gbins, tb, 0, h->stream, end, nbins, 0);
     hipLaunchKernelGGL(order_kernel, gb, tb, 0, h->stream, N, key_s, idx_s, wpos, start, end, spos);
-    const dim3 gs(static_cast<unsigned>((static_cast<long>(N) * NB_LANES + NB_THREADS - 1) / NB_THREADS));
-    hipLaunchKernelGGL((search_kernel<false, NB_LANES>), gs, tb, 0, h->stream, N, g, key, idx_s, start, end, wpos, spos,
-                       wrap, cnt, nullptr, nullptr, nullptr, h->d_err);
+    const auto search = [&](auto fill) {
+        for (long i0 = 0; i0 < N; i0 += NB_SLICE) {
+            const long n = std::min<long>(N - i0, NB_SLICE);
+            const dim3 gs(static_cast<unsigned>((n * NB_LANES + NB_THREADS - 1) / NB_THREADS));
+            hipLaunchKernelGGL((search_kernel<decltype(fill)::value, NB_LANES>), gs, tb, 0, h->stream,
+                               static_cast<int>(i0), static_cast<int>(i0 + n), g, key, idx_s, start, end, wpos, spos, wrap,
+                               cnt, offsets, nbr_j, shift, h->d_err);
+        }
+    };
+    search(std::false_type{});
     hipLaunchKernelGGL(fill_int_kernel, dim3(1), tb, 0, h->stream, reinterpret_cast<int*>(cnt + N), 2L, 0);
     tbytes = sT;
     if (rocprim::exclusive_scan(tmp, tbytes, cnt, off64, 0L, static_cast<size_t>(N) + 1, rocprim::plus<long>(),
@@ -331,8 +340,7 @@ int pod_build_neighbors(pod_handle* h, int N, const void* pos, const double* cel
     *n_pairs = P;
     if (P > 0x7fffffffL) return POD_ENOTSUP;   // int32 offsets
     if (P > 0 && capacity >= P) {
-        hipLaunchKernelGGL((search_kernel<true, NB_LANES>), gs, tb, 0, h->stream, N, g, key, idx_s, start, end, wpos,
-                           spos, wrap, nullptr, offsets, nbr_j, shift, h->d_err);
+        search(std::true_type{});
         if (hipStreamSynchronize(h->stream) != hipSuccess) return POD_EHIP;
     }
     return hipGetLastError() == hipSuccess ? POD_OK : POD_EHIP;
