@@ -143,6 +143,7 @@ __global__ __launch_bounds__(ST) void small_kernel(WideArgs<T> g) {
     const T pi[3] = {g.pos[3 * i], g.pos[3 * i + 1], g.pos[3 * i + 2]};
 
     // ---- 1. the pairs c0 .. c0 + nc - 1: geometry, radial functions, monomials
+    T dv[3] = {T(0), T(0), T(0)};   // this thread's pair vector, for the virial
     auto stage = [&](int c0, int nc, bool mono, int& err) {
         if (tid < nc) {
             const SlotIdx si = slot_index(g, true, beg + c0 + tid);
@@ -155,7 +156,10 @@ __global__ __launch_bounds__(ST) void small_kernel(WideArgs<T> g) {
             else radial<T, MODE == 1>(P, r, ri, R, dR);
             const T u[3] = {d[0] * ri, d[1] * ri, d[2] * ri};   // zero for a pair that is not a neighbour
 #pragma unroll
-            for (int x = 0; x < 3; ++x) sU[5 * tid + x] = u[x];
+            for (int x = 0; x < 3; ++x) {
+                sU[5 * tid + x] = u[x];
+                dv[x] = d[x];
+            }
             sU[5 * tid + 3] = ri;
             sU[5 * tid + 4] = ok ? r : T(0);
 #pragma unroll
@@ -363,7 +367,7 @@ __global__ __launch_bounds__(ST) void small_kernel(WideArgs<T> g) {
                 atomicAdd(&g.Facc[3 * i + 2], static_cast<double>(gz));
             }
             if (ok) {
-                const double dd[3] = {double(ux * r), double(uy * r), double(uz * r)};
+                const double dd[3] = {double(dv[0]), double(dv[1]), double(dv[2])};
                 const double gg[3] = {double(gx), double(gy), double(gz)};
 #pragma unroll
                 for (int x = 0; x < 3; ++x)
