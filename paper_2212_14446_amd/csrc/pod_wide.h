@@ -41,7 +41,7 @@ struct WideArgs {
 };
 
 // LDS layout of one wide_kernel workgroup, in bytes: the energy coefficients
-// (M), the monomial codes (NA ints) and factorials, 1 / a, with 4-body terms the
+// (M), the monomial codes (NA ints) and factorials, 1 / a!, with 4-body terms the
 // packed eq. (30a) tables (wide_tab_ints ints), the basis rows [K][row stride]
 // (later the adjoint rows), the degree sums [K][PA + 1] and their parts
 // [K][WIDE_PARTS], B_{k 0} (K), the pair records of a chunk [WIDE_CHUNK][4 +
@@ -86,7 +86,7 @@ __host__ __device__ constexpr WideLds wide_lds(int K, int PA, int M, bool four, 
     L.code = wide_align(L.coef + (energy ? static_cast<size_t>(M) * ts : 0));
     L.fact = wide_align(L.code + NA * sizeof(int));
     L.inv = wide_align(L.fact + NA * sizeof(float));
-    L.tab = wide_align(L.inv + (POD_MAX_P + 1) * ts);
+    L.tab = wide_align(L.inv + (POD_MAX_P + 1) * sizeof(double));
     L.b = wide_align(L.tab + (four ? static_cast<size_t>(energy ? wide_tab_ints() : wide_desc_ints()) * sizeof(int) : 0));
     L.s = wide_align(L.b + static_cast<size_t>(K) * wide_row(static_cast<int>(NA)) * ts);
     L.part = wide_align(L.s + static_cast<size_t>(K) * (PA + 1) * ts);

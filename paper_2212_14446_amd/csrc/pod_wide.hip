@@ -150,15 +150,23 @@ template <> struct Mx<float> {
     static __device__ __forceinline__ int row(int g, int e) { return 4 * g + e; }
 };
 
-// Divided powers u^a / a!, a = 0 .. PA, behind a leading zero (inv[a] = 1 / a).
+// Divided powers u^a / a!, a = 0 .. PA, behind a leading zero (inv[a] = 1 / a!).
+// The power runs in double and is divided once, so that an FP32 entry has one
+// rounding, and an FP64 entry the power's and one more (the quotient is corrected
+// by its remainder).  With one factor u * (1 / a) per step the rounding of 1 / 3,
+// 1 / 5, ... was the same for every pair and atom: degree 10 of the descriptors
+// was off by 2.2e-7 on average in FP32, now by 2e-8 as with plain powers.
 template <typename T>
-__device__ __forceinline__ void divided_powers(T* pw, T u, int PA, const T* inv) {
+__device__ __forceinline__ void divided_powers(T* pw, T u, int PA, const double* inv) {
     pw[0] = T(0);
-    T v = T(1);
-    pw[1] = v;
+    double v = 1.0, f = 1.0;
+    pw[1] = T(1);
     for (int a = 1; a <= PA; ++a) {
-        v *= u * inv[a];
-        pw[a + 1] = v;
+        v *= static_cast<double>(u);
+        f *= a;
+        double q = v * inv[a];
+        if (sizeof(T) == 8) q = fma(fma(-q, f, v), inv[a], q);
+        pw[a + 1] = static_cast<T>(q);
     }
 }
 
@@ -260,7 +268,7 @@ __device__ __forceinline__ void wide_body(const WideArgs<T>& g) {
     T* sP = reinterpret_cast<T*>(smem + L.pw);
     __shared__ int sPartDef[WIDE_PARTS];
     auto part_begin_of = [](int a) { return kParts.begin[a]; };   // parts of the degrees below a
-    T* sInv = reinterpret_cast<T*>(smem + L.inv);
+    double* sInv = reinterpret_cast<double*>(smem + L.inv);
     T* sG4 = reinterpret_cast<T*>(smem + L.g);     // [wavefront][q][4]
     float* sFact = reinterpret_cast<float*>(smem + L.fact);   // a! b! c!
     double* sRed = reinterpret_cast<double*>(smem + L.red);
@@ -268,7 +276,11 @@ __device__ __forceinline__ void wide_body(const WideArgs<T>& g) {
     const int lane = tid % WAVE, wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int c16 = lane & 15, gq = lane >> 4;
 
-    if (tid <= POD_MAX_P) sInv[tid] = T(1) / T(tid > 0 ? tid : 1);
+    if (tid <= POD_MAX_P) {
+        double f = 1.0;
+        for (int a = 2; a <= tid; ++a) f *= a;
+        sInv[tid] = 1.0 / f;
+    }
     for (int n = tid; n < NA; n += WT) {
         const int cd = kWide.code[n];
         sCode[n] = cd;
