@@ -235,7 +235,7 @@ typedef struct pod_tune {
     int nblocks;  /* persistent dG/dR workgroups (0 = one per cell, radial index
                      and chunk) */
     int threads;  /* threads per dG/dR workgroup, a multiple of 64 up to 512
-                     (0 = library's choice; otherwise POD_EINVAL) */
+                     (0 = library's choice, which may be more; otherwise POD_EINVAL) */
 } pod_tune;
 
 int pod_batch_assemble(pod_handle* h, int n_cfg, int N, int P, const int* cfg_atom_off,

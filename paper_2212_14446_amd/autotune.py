@@ -1,8 +1,9 @@
 """Autotuner of the batched assembly's launch shape.
 
 pod_batch_assemble takes a pod_tune triple (cw, nblocks, threads):
-descriptor columns per dG/dR chunk, persistent workgroups and threads per
-workgroup.
+descriptor columns per dG/dR chunk, workgroups and threads per workgroup, 0
+for the library's choice of each (of the workgroups: one per cell, radial index
+and chunk).
 The best triple depends on the batch (cell sizes, pair counts) and on the
 descriptor set (M, K, angular degree).  This module times a fixed candidate
 list through the library (HIP events on the handle's stream), picks the
@@ -25,9 +26,15 @@ import numpy as np
 
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "pod_batch_tune.json")
 
-CW = (6, 9, 12, 17)
-NBLOCKS = (256, 512, 1024)
-THREADS = (256, 512)
+# The library's own choice comes first: another shape has to beat it by the
+# margin.  Fewer workgroups than items never did (2,000 cells up to 250 atoms, one chunk:
+# 3,618 us of kernels with one per item, 3,584 with 1,024, 3,830 with 256).
+CW = (0, 6, 9, 12, 17)
+NBLOCKS = (0,)
+THREADS = (0, 256, 512)
+# Revision of the batched kernels' launch shapes: picks measured on kernels of
+# another revision are measured again.
+KERNELS = 2
 
 
 def candidates(cw: Iterable[int] = CW, nblocks: Iterable[int] = NBLOCKS, threads: Iterable[int] = THREADS):
@@ -37,14 +44,14 @@ def candidates(cw: Iterable[int] = CW, nblocks: Iterable[int] = NBLOCKS, threads
 
 def signature(n_cfg: int, cell_atoms: Sequence[int], cell_pairs: Sequence[int], M: int, K: int, PA: int,
               device: str = "") -> str:
-    """Cache key: the descriptor set and a coarse summary of the batch (cell
-    count, totals, largest cell, a histogram of cell sizes)."""
+    """Cache key: the kernels' revision, the descriptor set and a coarse summary
+    of the batch (cell count, totals, largest cell, a histogram of cell sizes)."""
     a = np.asarray(cell_atoms, dtype=np.int64)
     p = np.asarray(cell_pairs, dtype=np.int64)
     hist = np.histogram(a, bins=8, range=(0, max(int(a.max(initial=0)), 1) + 1))[0] if a.size else []
     desc = {"n_cfg": int(n_cfg), "N": int(a.sum()), "P": int(p.sum()), "max_atoms": int(a.max(initial=0)),
             "max_pairs": int(p.max(initial=0)), "hist": [int(x) for x in hist], "M": int(M), "K": int(K),
-            "PA": int(PA), "device": device}
+            "PA": int(PA), "device": device, "kernels": KERNELS}
     return hashlib.sha1(json.dumps(desc, sort_keys=True).encode()).hexdigest()[:16]
 
 
@@ -118,14 +125,18 @@ def batch_signature(model, batch) -> str:
 
 def measure_batch(model, batch, reps: int = 3, outputs=None):
     """A measure(c) for tune(): mean kernel time of pod_batch_assemble with
-    launch shape c (one untimed warm-up call, then `reps` timed calls)."""
+    launch shape c (one untimed warm-up call, before the first shape `reps` more,
+    then `reps` timed calls)."""
     from . import pod
     o = outputs
+    warm = reps
 
     def run(c):
-        nonlocal o
+        nonlocal o, warm
         try:
-            o = pod.batch_assemble(model, batch, tune=c, check=False, out=o)
+            for _ in range(1 + warm):
+                o = pod.batch_assemble(model, batch, tune=c, check=False, out=o)
+            warm = 0
             pod.pod_check(model.h)
             pod.pod_set_kernel_timing(model.h, reps)
             for _ in range(reps):
