@@ -232,8 +232,8 @@ typedef struct pod_tune {
     int cw;       /* most descriptor columns per dG/dR chunk (0 = library's
                      choice; lowered until the cell's LDS accumulator fits the
                      device's LDS per workgroup) */
-    int nblocks;  /* persistent dG/dR workgroups (0 = one per cell, radial index
-                     and chunk) */
+    int nblocks;  /* cells whose dG/dR is worked on at a time, each by one
+                     workgroup per radial index and chunk (0 = all) */
     int threads;  /* threads per dG/dR workgroup, a multiple of 64 up to 512
                      (0 = library's choice, which may be more; otherwise POD_EINVAL) */
 } pod_tune;

@@ -1,9 +1,8 @@
 """Autotuner of the batched assembly's launch shape.
 
 pod_batch_assemble takes a pod_tune triple (cw, nblocks, threads):
-descriptor columns per dG/dR chunk, workgroups and threads per workgroup, 0
-for the library's choice of each (of the workgroups: one per cell, radial index
-and chunk).
+descriptor columns per dG/dR chunk, cells worked on at a time and threads per
+workgroup, 0 for the library's choice of each (all cells).
 The best triple depends on the batch (cell sizes, pair counts) and on the
 descriptor set (M, K, angular degree).  This module times a fixed candidate
 list through the library (HIP events on the handle's stream), picks the
@@ -27,8 +26,7 @@ import numpy as np
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "pod_batch_tune.json")
 
 # The library's own choice comes first: another shape has to beat it by the
-# margin.  Fewer workgroups than items never did (2,000 cells up to 250 atoms, one chunk:
-# 3,618 us of kernels with one per item, 3,584 with 1,024, 3,830 with 256).
+# margin.  Fewer cells at a time than all never did.
 CW = (0, 6, 9, 12, 17)
 NBLOCKS = (0,)
 THREADS = (0, 256, 512)

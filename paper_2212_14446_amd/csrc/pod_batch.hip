@@ -49,6 +49,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "pod.h"
@@ -65,6 +66,8 @@ using namespace dev;
 struct BArgs {
     ParamsT<double> prm;  // by value: read with scalar loads
     int n_cell;           // cells of this launch
+    int c_end;            // one past the last of them
+    long ent_max;         // record entries of the largest
     const int* order;     // their processing order (decreasing pair count)
     const int* cfg_off;   // n_cfg + 1 atom offsets
     const double* pos;
@@ -284,34 +287,45 @@ __device__ __forceinline__ void class_task(const int* recJ, const RowList* sL, i
     }
 }
 
-// ---- 1. pair records: one workgroup per cell ----
+// ---- 1. pair records: workgroups (cell, part), one entry (slot, atom) per
+// thread and turn, consecutive threads on consecutive entries of the cell ----
+// Lanes on the atoms of a cell and its four wavefronts on the slots, as before,
+// left most lanes idle and a serial chain of a quarter of the longest list: 64
+// cells of 2 to 10 atoms 35 us, 200 cells up to 250 atoms (K = 2) 89 us.
+// DERIV: with R'_m; without derivatives only R_m is read back.
 constexpr int REC_THREADS = 256;
-template <bool FAST>
+// Workgroups aimed at, one turn and a half of the chip: more of them read a cell's
+// lists and positions into more caches (2,000 cells: one part each 303 us, four
+// 351, sixteen 377; 314 before).
+constexpr int REC_BLOCKS = 2048;
+
+template <bool FAST, bool DERIV>
 __global__ __launch_bounds__(REC_THREADS) void batch_record_kernel(BArgs g) {
     __shared__ double sQ[POD_MAX_L * POD_MAX_K];
     const ParamsT<double>* __restrict__ P = &g.prm;
     const int K = P->K;
-    const int tid = threadIdx.x;
-    if (FAST)
-        for (int i = tid; i < POD_MAX_L * POD_MAX_K; i += REC_THREADS) sQ[i] = (&P->Q[0][0])[i];
-    __syncthreads();
+    const unsigned tid = threadIdx.x;
     const int c = g.order[blockIdx.x];
     const int a0 = g.cfg_off[c], a1 = g.cfg_off[c + 1];
+    const unsigned Nc = a1 - a0;
+    const long eb0 = g.ebase[c];
+    const long n_ent = (c + 1 < g.c_end ? g.ebase[c + 1] : g.n_ent) - eb0;
+    const unsigned first = blockIdx.y * REC_THREADS, step = gridDim.y * REC_THREADS;
+    if (first >= n_ent) return;   // empty cells too
+    if (FAST) {
+        for (unsigned i = tid; i < POD_MAX_L * POD_MAX_K; i += REC_THREADS) sQ[i] = (&P->Q[0][0])[i];
+        __syncthreads();
+    }
     const double* cell = g.cells + 9 * static_cast<size_t>(c);
     const double rin = P->rin, rcut = P->rcut;
     int eb = 0;
-    const int Nc = a1 - a0;
-    const long eb0 = g.ebase[c];
-    // lanes take consecutive atoms, wavefronts the slots: records are written
-    // (and read back) contiguously over the atoms
-    const int lane = tid & 63, wv = tid >> 6;
-    for (int ab = 0; ab < Nc; ab += WAVE) {
-        const int al = ab + lane;
-        const int i = a0 + min(al, Nc - 1);
-        const double xi = g.pos[3 * i + 0], yi = g.pos[3 * i + 1], zi = g.pos[3 * i + 2];
-        const int pb = g.offsets[i], cnt = al < Nc ? g.offsets[i + 1] - pb : 0;
-        for (int s = wv; s < cnt; s += REC_THREADS / WAVE) {
-            const int p = pb + s;
+    const unsigned ds = step / Nc, da = step - ds * Nc;
+    unsigned s = (first + tid) / Nc, al = first + tid - s * Nc;
+    for (long q = eb0 + first + tid; q < eb0 + n_ent; q += step) {
+        const int i = a0 + static_cast<int>(al);
+        const int p = g.offsets[i] + static_cast<int>(s);
+        if (p < g.offsets[i + 1]) {   // lists shorter than the cell's longest leave entries unused
+            const double xi = g.pos[3 * i + 0], yi = g.pos[3 * i + 1], zi = g.pos[3 * i + 2];
             const int j = g.nbr_j[p];
             const int sh = g.shift[p];
             double d0 = 0, d1 = 0, d2 = 0, r = 0.5 * (rin + rcut);
@@ -334,9 +348,8 @@ __global__ __launch_bounds__(REC_THREADS) void batch_record_kernel(BArgs g) {
             }
             const double ri = 1.0 / r;
             double R[FAST_MAX_K], dR[FAST_MAX_K];
-            if constexpr (FAST) radial_std<double, true>(P, sQ, r, ri, R, dR);
-            else radial<double, true>(P, r, ri, R, dR);
-            const long q = eb0 + static_cast<long>(s) * Nc + al;
+            if constexpr (FAST) radial_std<double, DERIV>(P, sQ, r, ri, R, dR);
+            else radial<double, DERIV>(P, r, ri, R, dR);
             g.recJ[q] = j >= a0 && j < a1 ? j - a0 : -1;
             double2* U2 = reinterpret_cast<double2*>(g.recU) + 2 * q;
             U2[0] = ok ? double2{d0 * ri, d1 * ri} : double2{0.0, 0.0};
@@ -344,8 +357,12 @@ __global__ __launch_bounds__(REC_THREADS) void batch_record_kernel(BArgs g) {
 #pragma unroll
             for (int k = 0; k < FAST_MAX_K; ++k)
                 if (k < K)
-                    reinterpret_cast<double2*>(g.recR)[k * g.n_ent + q] = ok ? double2{R[k], dR[k]} : double2{0.0, 0.0};
+                    reinterpret_cast<double2*>(g.recR)[k * g.n_ent + q] =
+                        ok ? double2{R[k], DERIV ? dR[k] : 0.0} : double2{0.0, 0.0};
         }
+        s += ds;
+        al += da;
+        if (al >= Nc) { al -= Nc; ++s; }
     }
     eb = wave_or(eb);
     if ((tid & 63) == 0 && eb) atomicOr(g.err, eb);
@@ -577,9 +594,13 @@ __global__ __launch_bounds__(deriv_threads(PA)) void batch_deriv_kernel(BArgs g)
 }
 
 template <int PA>
-hipError_t launch_batch(const BArgs& a, bool fast, int nitem, int nth, size_t lds, hipStream_t st) {
-    if (fast) hipLaunchKernelGGL((batch_record_kernel<true>), dim3(a.n_cell), dim3(REC_THREADS), 0, st, a);
-    else hipLaunchKernelGGL((batch_record_kernel<false>), dim3(a.n_cell), dim3(REC_THREADS), 0, st, a);
+hipError_t launch_batch(const BArgs& a, bool fast, int ncell, int nth, size_t lds, hipStream_t st) {
+    const auto records = [&](auto kernel) {
+        const long parts = std::min((a.ent_max + REC_THREADS - 1) / REC_THREADS, static_cast<long>(REC_BLOCKS / a.n_cell));
+        hipLaunchKernelGGL(kernel, dim3(a.n_cell, static_cast<unsigned>(std::max(parts, 1L))), dim3(REC_THREADS), 0, st, a);
+    };
+    if (fast) records(a.dGdR ? batch_record_kernel<true, true> : batch_record_kernel<true, false>);
+    else records(a.dGdR ? batch_record_kernel<false, true> : batch_record_kernel<false, false>);
     hipLaunchKernelGGL((batch_basis_kernel<PA>), dim3(a.n_cell), dim3(BASIS_THREADS),
                        static_cast<size_t>(a.prm.M) * sizeof(double), st, a);
     hipError_t e = hipGetLastError();
@@ -589,24 +610,25 @@ hipError_t launch_batch(const BArgs& a, bool fast, int nitem, int nth, size_t ld
         return hipErrorInvalidValue;
     // one workgroup per item, as far as a launch's 2^32 threads reach: the
     // kernel's loop takes the rest
-    const long all = (a.n_cell + 7L) / 8 * 8 * a.prm.K * a.nch;
-    const int most = static_cast<int>(std::min(all, 1L << 22));
-    if (nitem <= 0 || nitem > most) nitem = most;
+    // (ncell: cells worked on at a time)
+    const long per_cell = static_cast<long>(a.prm.K) * a.nch;
+    const long all = ((ncell > 0 ? std::min(ncell, a.n_cell) : a.n_cell) + 7L) / 8 * 8 * per_cell;
+    const int nitem = static_cast<int>(std::min(all, 1L << 22));
     if (nth <= 0) nth = deriv_threads(PA);
     if (nth > deriv_threads(PA)) nth = deriv_threads(PA);
     hipLaunchKernelGGL((batch_deriv_kernel<PA>), dim3(nitem), dim3(nth), lds, st, a);
     return hipGetLastError();
 }
 
-hipError_t dispatch_batch(int PA, const BArgs& a, bool fast, int nitem, int nth, size_t lds, hipStream_t st) {
+hipError_t dispatch_batch(int PA, const BArgs& a, bool fast, int ncell, int nth, size_t lds, hipStream_t st) {
     switch (PA) {
-        case 0: return launch_batch<0>(a, fast, nitem, nth, lds, st);
-        case 1: return launch_batch<1>(a, fast, nitem, nth, lds, st);
-        case 2: return launch_batch<2>(a, fast, nitem, nth, lds, st);
-        case 3: return launch_batch<3>(a, fast, nitem, nth, lds, st);
-        case 4: return launch_batch<4>(a, fast, nitem, nth, lds, st);
-        case 5: return launch_batch<5>(a, fast, nitem, nth, lds, st);
-        case 6: return launch_batch<6>(a, fast, nitem, nth, lds, st);
+        case 0: return launch_batch<0>(a, fast, ncell, nth, lds, st);
+        case 1: return launch_batch<1>(a, fast, ncell, nth, lds, st);
+        case 2: return launch_batch<2>(a, fast, ncell, nth, lds, st);
+        case 3: return launch_batch<3>(a, fast, ncell, nth, lds, st);
+        case 4: return launch_batch<4>(a, fast, ncell, nth, lds, st);
+        case 5: return launch_batch<5>(a, fast, ncell, nth, lds, st);
+        case 6: return launch_batch<6>(a, fast, ncell, nth, lds, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -646,7 +668,7 @@ int pod_batch_assemble(pod_handle* h, int n_cfg, int N, int P, const int* cfg_at
     const size_t base_bytes = ((sizeof(long) * n_cfg + 255) / 256) * 256;
     BatchRounds rounds;
     rc = fit_rounds(
-        n_cfg, coff.data(), off.data(), per_ent, per_atom, SCRATCH_CAP,
+        n_cfg, coff.data(), plan.longest.data(), per_ent, per_atom, SCRATCH_CAP,
         [&](size_t bytes) {
             const int r = ensure_scratch(h, order_bytes + base_bytes + bytes + 256);
             if (r == POD_ENOMEM) (void)hipGetLastError();   // answered here, not by the next launch
@@ -664,10 +686,13 @@ int pod_batch_assemble(pod_handle* h, int n_cfg, int N, int P, const int* cfg_at
         for (int c : plan.order)
             order[at[std::upper_bound(first.begin(), first.end(), c) - first.begin() - 1]++] = c;
     }
+    // both tables in one copy (a second one costs about 8 us)
+    std::vector<char> tables(order_bytes + base_bytes);
+    std::memcpy(tables.data(), order.data(), sizeof(int) * n_cfg);
+    std::memcpy(tables.data() + order_bytes, rounds.ebase.data(), sizeof(long) * n_cfg);
     int* d_order = static_cast<int*>(h->d_scratch);
     long* d_ebase = reinterpret_cast<long*>(static_cast<char*>(h->d_scratch) + order_bytes);
-    if (hipMemcpyAsync(d_order, order.data(), sizeof(int) * n_cfg, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
-        hipMemcpyAsync(d_ebase, rounds.ebase.data(), sizeof(long) * n_cfg, hipMemcpyHostToDevice, h->stream) != hipSuccess)
+    if (hipMemcpyAsync(h->d_scratch, tables.data(), tables.size(), hipMemcpyHostToDevice, h->stream) != hipSuccess)
         return POD_EHIP;
     BArgs a;
     a.prm = h->hp_d;
@@ -703,6 +728,8 @@ int pod_batch_assemble(pod_handle* h, int n_cfg, int N, int P, const int* cfg_at
     for (size_t k = 0; k + 1 < first.size() && e == hipSuccess; ++k) {
         const int c0 = first[k], c1 = first[k + 1];
         a.n_cell = c1 - c0;
+        a.c_end = c1;
+        a.ent_max = rounds.ent_max[k];
         a.order = d_order + c0;
         a.a_base = coff[c0];
         a.n_ent = rounds.n_ent[k];

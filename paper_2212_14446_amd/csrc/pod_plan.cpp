@@ -205,32 +205,34 @@ int open_geometry(const double* pos, int N, double rlist, NbGeom* g) {
     return POD_OK;
 }
 
-void plan_rounds(int n_cfg, const int* coff, const int* off, size_t per_ent, size_t per_atom, size_t cap,
+void plan_rounds(int n_cfg, const int* coff, const int* longest, size_t per_ent, size_t per_atom, size_t cap,
                  BatchRounds* r) {
     r->first.assign(1, 0);
     r->ebase.resize(n_cfg);
     r->n_ent.clear();
+    r->ent_max.clear();
     r->bytes = 0;
     size_t bytes = 0;
-    long ent = 0;
+    long ent = 0, ent_max = 0;
     for (int c = 0; c < n_cfg; ++c) {
-        int longest = 0;
-        for (int i = coff[c]; i < coff[c + 1]; ++i) longest = std::max(longest, off[i + 1] - off[i]);
-        const long nc = coff[c + 1] - coff[c], e = longest * nc;
+        const long nc = coff[c + 1] - coff[c], e = longest[c] * nc;
         const size_t need = static_cast<size_t>(e) * per_ent + static_cast<size_t>(nc) * per_atom;
         if (c > r->first.back() && (bytes + need > cap || c - r->first.back() >= BATCH_MAX_CELLS)) {
             r->first.push_back(c);
             r->n_ent.push_back(ent);
+            r->ent_max.push_back(ent_max);
             r->bytes = std::max(r->bytes, bytes);
             bytes = 0;
-            ent = 0;
+            ent = ent_max = 0;
         }
         r->ebase[c] = ent;
         ent += e;
+        ent_max = std::max(ent_max, e);
         bytes += need;
     }
     r->first.push_back(n_cfg);
     r->n_ent.push_back(ent);
+    r->ent_max.push_back(ent_max);
     r->bytes = std::max(r->bytes, bytes);
 }
 
@@ -239,12 +241,21 @@ int plan_batch(int n_cfg, int N, int P, const int* coff, const int* off, int M, 
     if (n_cfg < 1 || N < 0 || P < 0 || !coff || !off || !plan || M < 1) return POD_EINVAL;
     if (coff[0] != 0 || coff[n_cfg] != N || off[0] != 0 || off[N] != P) return POD_EINVAL;
     std::vector<int> npair(n_cfg);
+    plan->longest.resize(n_cfg);
     int max_nc = 0, max_pc = 0;
     for (int c = 0; c < n_cfg; ++c) {
         if (coff[c + 1] < coff[c] || coff[c + 1] > N) return POD_EINVAL;
         const int nc = coff[c + 1] - coff[c];
-        for (int a = coff[c]; a < coff[c + 1]; ++a)
-            if (off[a + 1] < off[a]) return POD_ENEIGH;
+        // without an early exit, so that the pass over the atoms vectorises
+        // (unsigned: differences of malformed offsets may be out of range)
+        bool decreases = false;
+        unsigned most = 0;
+        for (int a = coff[c]; a < coff[c + 1]; ++a) {
+            decreases |= off[a + 1] < off[a];
+            most = std::max(most, static_cast<unsigned>(off[a + 1]) - static_cast<unsigned>(off[a]));
+        }
+        if (decreases) return POD_ENEIGH;
+        plan->longest[c] = static_cast<int>(most);
         npair[c] = off[coff[c + 1]] - off[coff[c]];
         max_nc = std::max(max_nc, nc);
         max_pc = std::max(max_pc, npair[c]);

@@ -72,7 +72,7 @@ constexpr int BATCH_MAX_THREADS = 512;
 // round's cells are in scratch at a time.  Cells are taken in order; a round
 // ends before the cell that would take its scratch beyond cap bytes (a cell
 // that needs more by itself has a round of its own) or after BATCH_MAX_CELLS
-// cells (a launch has at most 2^32 threads).  A cell has longest list
+// cells (a launch has at most 2^32 threads).  A cell has longest[cell]
 // x atoms record entries of per_ent bytes (lists padded to the cell's longest)
 // and per_atom bytes for every atom.
 constexpr int BATCH_MAX_CELLS = 1 << 20;
@@ -81,24 +81,25 @@ struct BatchRounds {
     std::vector<int> first;      // first cell of every round, then n_cfg
     std::vector<long> ebase;     // first record entry of every cell within its round
     std::vector<long> n_ent;     // record entries of every round
+    std::vector<long> ent_max;   // record entries of its largest cell
     size_t bytes;                // scratch of the largest round
 };
 
-void plan_rounds(int n_cfg, const int* coff, const int* off, size_t per_ent, size_t per_atom, size_t cap,
+void plan_rounds(int n_cfg, const int* coff, const int* longest, size_t per_ent, size_t per_atom, size_t cap,
                  BatchRounds* r);
 
 // The rounds for which alloc(bytes of scratch) does not answer POD_ENOMEM: of at
 // most cap bytes, else of half as much, and so on down to the largest cell's own.
 // Returns alloc's last answer.
 template <typename Alloc>
-int fit_rounds(int n_cfg, const int* coff, const int* off, size_t per_ent, size_t per_atom, size_t cap, Alloc alloc,
+int fit_rounds(int n_cfg, const int* coff, const int* longest, size_t per_ent, size_t per_atom, size_t cap, Alloc alloc,
                BatchRounds* r) {
-    plan_rounds(n_cfg, coff, off, per_ent, per_atom, cap, r);
+    plan_rounds(n_cfg, coff, longest, per_ent, per_atom, cap, r);
     for (;;) {
         const int rc = alloc(r->bytes);
         if (rc != POD_ENOMEM) return rc;
         const size_t tried = r->bytes;
-        plan_rounds(n_cfg, coff, off, per_ent, per_atom, tried / 2, r);
+        plan_rounds(n_cfg, coff, longest, per_ent, per_atom, tried / 2, r);
         if (r->bytes >= tried) return rc;   // the largest cell alone
     }
 }
@@ -106,14 +107,14 @@ int fit_rounds(int n_cfg, const int* coff, const int* off, size_t per_ent, size_
 // Launch plan of pod_batch_assemble from host copies of the cell atom
 // offsets coff[n_cfg + 1] and the pair offsets off[N + 1]: the widest chunk
 // (largest that fits lds_max, from the tuning value or 17 down), the atoms of
-// the LDS accumulator and the processing order of the cells (decreasing pair
-// count, stable).  The other fields describe the plan (cell and pair maxima, LDS
+// the LDS accumulator, the processing order of the cells (decreasing pair
+// count, stable) and the longest pair list of each cell.  The other fields describe the plan (cell and pair maxima, LDS
 // bytes at that width, a workgroup and thread count); the launch itself takes
 // its grid from the cells and its threads from the tuning value or its own rule.
 struct BatchPlan {
     int cw, nblk, nth, nc_max, max_nc, max_pc;
     size_t lds;
-    std::vector<int> order;
+    std::vector<int> order, longest;
 };
 
 // POD_EINVAL for offsets that do not start at 0, end at N / P or decrease
