@@ -1001,24 +1001,28 @@ hipError_t launch_finalize(const FinArgs<T>& f, int nblk, const MdStep* md, hipS
 }
 
 // Reverse-pair index: for pair p = (i -> j, n) find the first q = (j -> i,
-// -n) in the list of j.  REV_LANES lanes serve one pair and compare
-// consecutive entries of j's list, so a step reads one or two cache lines
-// per pair (one lane per pair walked 64 lists at once: 21 us for the
-// 15,840-atom list, 1.13 ms for the 1,024,000-atom one).
-constexpr int REV_LANES = 8;
+// -n) in the list of j.  G lanes serve one pair and compare consecutive
+// entries of j's list, so a step reads one cache line per pair or two; LPA lanes
+// serve one atom.  Bound by the latency of those dependent reads on small
+// systems and by the reads themselves on large ones.  One lane per pair / eight
+// lanes / this, us per call: 128 atoms 7.2 / 9.2 / 5.6, 2,000 7.8 / 9.6 / 5.7, 15,840
+// (FP64 list of 26 pairs an atom) 19.0 / 13.6 / 11.9, 54,000 64.9 / 61.0 / 51.8, 524,288
+// 472 / 482 / 411, 1,024,000 1,134 / 1,175 / 1,004; 128 atoms with 242 pairs each
+// 312 / 295 / 151.
+template <int LPA, int G>
 __global__ __launch_bounds__(256) void reverse_kernel(const int* __restrict__ offsets, const int* __restrict__ nbr_j,
                                                       const int* __restrict__ shift, int N, int P, int* rev,
                                                       int* err) {
-    constexpr int G = REV_LANES;
-    const int a = blockIdx.x * 8 + static_cast<int>(threadIdx.x) / 32;
-    const int s0 = static_cast<int>(threadIdx.x % 32) / G, sub = threadIdx.x % G, lane = threadIdx.x % WAVE;
+    const int a = blockIdx.x * (256 / LPA) + static_cast<int>(threadIdx.x) / LPA;
+    const int s0 = static_cast<int>(threadIdx.x % LPA) / G, sub = threadIdx.x % G, lane = threadIdx.x % WAVE;
     if (a >= N) return;
     const int b = offsets[a], e = offsets[a + 1];
     if (b < 0 || e < b || e > P) {
         if (s0 == 0 && sub == 0) atomicOr(err, ERR_NEIGH);
         return;
     }
-    for (int p = b + s0; p < e; p += 32 / G) {
+    // (unsigned: a list may end at 2^31 - 1)
+    for (unsigned p = static_cast<unsigned>(b) + s0; p < static_cast<unsigned>(e); p += LPA / G) {
         const int j = nbr_j[p];
         const int sh = shift[p];
         int found = -1;
@@ -1027,15 +1031,15 @@ __global__ __launch_bounds__(256) void reverse_kernel(const int* __restrict__ of
                             (((-unpack_shift(sh, 2)) & 0xFF) << 16);
             const int jb = offsets[j], je = offsets[j + 1];
             if (jb >= 0 && je >= jb && je <= P)
-                for (int q0 = jb; q0 < je && found < 0; q0 += 2 * G) {
-                    const int qa = q0 + sub, qb = qa + G;
-                    const int na = qa < je ? nbr_j[qa] : -1, nb = qb < je ? nbr_j[qb] : -1;
+                for (unsigned q0 = jb; q0 < static_cast<unsigned>(je) && found < 0; q0 += 2 * G) {
+                    const unsigned qa = q0 + sub, qb = qa + G, qe = je;
+                    const int na = qa < qe ? nbr_j[qa] : -1, nb = qb < qe ? nbr_j[qb] : -1;
                     const bool ha = na == a && (shift[qa] & 0xFFFFFF) == neg;
                     const bool hb = nb == a && (shift[qb] & 0xFFFFFF) == neg;
                     const unsigned ma = static_cast<unsigned>(__ballot(ha) >> (lane - sub)) & ((1u << G) - 1u);
                     const unsigned mb = static_cast<unsigned>(__ballot(hb) >> (lane - sub)) & ((1u << G) - 1u);
-                    if (ma) found = q0 + __ffs(ma) - 1;
-                    else if (mb) found = q0 + G + __ffs(mb) - 1;
+                    if (ma) found = static_cast<int>(q0) + __ffs(ma) - 1;
+                    else if (mb) found = static_cast<int>(q0) + G + __ffs(mb) - 1;
                 }
         }
         if (sub == 0) {
@@ -1043,6 +1047,14 @@ __global__ __launch_bounds__(256) void reverse_kernel(const int* __restrict__ of
             if (found < 0) atomicOr(err, ERR_NEIGH);
         }
     }
+}
+
+template <int LPA, int G>
+void launch_reverse(const int* offsets, const int* nbr_j, const int* shift, int N, int P, int* rev, int* err,
+                    hipStream_t st) {
+    constexpr int APB = 256 / LPA;
+    hipLaunchKernelGGL((reverse_kernel<LPA, G>), dim3((N - 1) / APB + 1), dim3(256), 0, st, offsets, nbr_j, shift, N, P,
+                       rev, err);
 }
 
 template <typename T, int PA, int MODE>
@@ -1517,8 +1529,11 @@ int pod_neighbor_reverse(pod_handle* h, int N, int P, const int* offsets, const 
     if (N > 0 && !offsets) return POD_EINVAL;
     if (P > 0 && (!nbr_j || !shift || !rev)) return POD_EINVAL;
     if (N == 0) return POD_OK;
-    hipLaunchKernelGGL(pod::reverse_kernel, dim3((N + 7) / 8), dim3(256), 0, h->stream, offsets, nbr_j, shift, N, P,
-                       rev, h->d_err);
+    // a whole wavefront per atom while that leaves the chip room (128 atoms 5.6
+    // against 8.1 us with half of one, 16,000 11.9 / 12.1, 40,000 42.4 / 43.3, 54,000
+    // 54.9 / 51.8, 1,024,000 1,048 / 1,004)
+    if (N <= 32768) pod::launch_reverse<64, 4>(offsets, nbr_j, shift, N, P, rev, h->d_err, h->stream);
+    else pod::launch_reverse<32, 4>(offsets, nbr_j, shift, N, P, rev, h->d_err, h->stream);
     return hipGetLastError() == hipSuccess ? POD_OK : POD_EHIP;
 }
 
