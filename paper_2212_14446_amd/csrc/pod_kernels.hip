@@ -1201,7 +1201,7 @@ int descriptors_impl(pod_handle* h, int N, int P, const void* pos, const double*
         timing_end(h, 1);
         return e == hipSuccess ? POD_OK : POD_EHIP;
     }
-    if (small_path(h->K, h->PA, N)) {
+    if (small_path(h->K, h->K4, h->PA, N, P, SmallCall::descriptors)) {
         const WideArgs<T> w = wide_args(a);
         timing_begin(h, 1);
         const hipError_t e = launch_small<T>(w, h->PA, 0, h->std_ok != 0, h->stream);
@@ -1228,10 +1228,16 @@ struct EfScratch {
     size_t part, wpart, abar, centre, pdv, gown, rec, total;
 };
 
-EfScratch ef_scratch_layout(int N, int P, int K, int PA, int M, size_t tsize, bool back, bool gather, bool net) {
+bool energy_small(const pod_handle* h, int N, int P, bool back) {
+    return small_path(h->K, h->K4, h->PA, N, P, back ? SmallCall::forces : SmallCall::energy);
+}
+
+EfScratch ef_scratch_layout(int N, int P, int K, int PA, int M, size_t tsize, bool back, bool gather,
+                            bool small) {
     auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
-    const bool small = !net && small_path(K, PA, N);   // partials per atom, pair gradients only
-    const bool wide = small || wide_path(K, PA);             // one kernel, partials per persistent workgroup
+    // small: partials per atom, pair gradients only; wide: one kernel, partials
+    // per persistent workgroup
+    const bool wide = small || wide_path(K, PA);
     const int apw = WAVE / K;
     const size_t nblk = N <= 0 ? 0 : small ? static_cast<size_t>(N)
                                    : wide  ? static_cast<size_t>(wide_blocks(N))
@@ -1267,7 +1273,8 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
     const bool back = (F != nullptr) || (W != nullptr);
     const bool gather = rev != nullptr && F != nullptr;
     const int nblk_p = back ? (P + PAIR_BLOCK - 1) / PAIR_BLOCK : 0;
-    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, MODE == 2);
+    const bool small = MODE == 1 && energy_small(h, N, P, back);
+    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, small);
     a.coef = static_cast<const T*>(c);
     a.E_atom = static_cast<T*>(E_atom);
     a.part = reinterpret_cast<double*>(scratch + L.part);
@@ -1277,7 +1284,6 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
     a.want_G = G != nullptr;
     a.want_back = back;
     a.netw = netw; a.n_net = n_net;
-    const bool small = MODE == 1 && small_path(h->K, h->PA, N);
     if (small || wide_path(h->K, h->PA)) {
         if constexpr (MODE != 1) return POD_ENOTSUP;
         // wide-degree kernel, or one workgroup per atom of a small system:
@@ -1367,7 +1373,8 @@ int energy_forces_impl(pod_handle* h, int N, int P, const void* pos, const doubl
                        int n_net = 0, const MdStep* md = nullptr) {
     const bool back = (F != nullptr) || (W != nullptr);
     const bool gather = rev != nullptr && F != nullptr;
-    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, MODE == 2);
+    const bool small = MODE == 1 && energy_small(h, N, P, back);
+    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, small);
     int rc = ensure_scratch(h, L.total);
     if (rc != POD_OK) return rc;
     rc = ensure_force_acc(h, N);
@@ -1411,13 +1418,13 @@ int energy_forces_noalloc_impl(pod_handle* h, int N, int P, const void* pos, con
                                void* E_atom, double* E, void* F, double* W, double* G) {
     const bool back = (F != nullptr) || (W != nullptr);
     const bool gather = rev != nullptr && F != nullptr;
-    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, false);
+    const EfScratch L = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, energy_small(h, N, P, back));
     const size_t facc_bytes = (back && !gather) ? ((static_cast<size_t>(N) * 3 * sizeof(double) + 255) & ~size_t(255))
                                                 : 0;
     // What a call may need is part of the interface: the per-atom and pair
     // kernels' arrays with the gradients at two slots per pair, whichever
     // kernels take the call.
-    const EfScratch full = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, true);
+    const EfScratch full = ef_scratch_layout(N, P, h->K, h->PA, h->M, sizeof(T), back, gather, false);
     const size_t second = gather ? (static_cast<size_t>(P > 0 ? P : 1) * 3 * sizeof(T) + 255) & ~size_t(255) : 0;
     if (std::max(L.total, full.total + second) + facc_bytes > static_cast<size_t>(POD_STATIC_SCRATCH_BYTES))
         return POD_ETOOBIG;

@@ -24,7 +24,26 @@ inline int small_max(int PA) { return PA <= 4 ? 1024 : 512; }
 // workgroups per compute unit), 128 above (1,024 atoms: 35.0 against 28.4 us).
 constexpr int SMALL_WIDE_N = 512;
 
-inline bool small_path(int K, int PA, int N) { return !wide_path(K, PA) && N <= small_max(PA); }
+// With short lists the per-atom kernel has little left to do in turn: K lanes take
+// an atom's list K pairs a round, P / (N K) rounds, while this path still brings
+// the tables of the 4-body terms to every atom.  Per-atom kernel / this path, us:
+//   forces: ahead from the first pair on (0.4 pairs per atom: at most 0.94 of the
+//     other), so only 4-body models without any pair go the other way (K = 8, degree
+//     6: 30 / 44);
+//   descriptors and energy alone, degree up to 4, FP32: N <= 512 1.0 round (K = 8)
+//     10.1 / 10.6, 1.8 rounds 10.6 / 10.7, 2.3 (K = 6) 11.1 / 9.7; above 512 atoms 1.8
+//     rounds 10.6 / 12.5, 2.3 11.1 / 11.5, 2.8 (K = 5) 10.8 / 10.0, 3.3 (K = 8) 14.8 /
+//     13.1; without 4-body terms 0.7 rounds (K = 6) 7.6 / 7.6 at any N;
+//   above degree 4, descriptors with 4-body terms: 1.8 rounds 15.9 / 19.6, 2.5 18.1 /
+//     19.7, 3.3 21.7 / 20.3; others 0.4 rounds 1.03 of the other, 0.6 0.88.
+enum class SmallCall { descriptors, energy, forces };
+inline bool small_path(int K, int K4, int PA, int N, int P, SmallCall call) {
+    if (wide_path(K, PA) || N > small_max(PA)) return false;
+    if (call == SmallCall::forces) return P > 0 || K4 == 0;
+    const long p2 = 2L * P, round = static_cast<long>(K) * N;   // p2 / round: twice the rounds
+    if (PA > 4) return p2 >= (call == SmallCall::descriptors && K4 > 0 ? 6 : 1) * round;
+    return p2 >= (K4 == 0 ? 2 : N <= SMALL_WIDE_N ? 4 : 5) * round;
+}
 
 // mode 0: descriptors; mode 1: energy, and with want_back the pair gradients.
 // One workgroup per atom; block partials [10 + M][N] and [9][N] (the layout of
