@@ -147,9 +147,10 @@ __host__ __device__ inline AtomLds atom_lds_layout(int K, int NA, int M, size_t 
 // atoms' adjoint rows (pair kernel) and pair gradients (finalize kernel),
 // which are then fetched once into that XCD's L2.  The number of blocks n comes
 // from the kernel's arguments: reading gridDim is one more dependent load before
-// any work (0.3 us a kernel; 15,840 atoms 59.4 -> 58.8 us).  Descriptors alone
-// keep the plain order: they read nothing that a neighbouring block writes
-// (500,000 atoms 472 us either way).
+// any work (0.3 us a kernel; 15,840 atoms 59.4 -> 58.8 us).  Descriptors and
+// energies alone keep the plain order: nothing that they write is read again
+// (energies of 432,000 atoms, K = 4, degree 3, FP32 194 us renumbered / 180; 128,000
+// atoms, K = 7, degree 6, FP64, 84 pairs 795 / 783; others the same).
 __device__ __forceinline__ int xcd_block(int i, int n) {
     constexpr int NX = 8;
     const int x = i % NX, k = i / NX;
@@ -181,7 +182,8 @@ __device__ __forceinline__ void atom_body(const KArgs<T>& g) {
     const int nw = MODE == 2 ? static_cast<int>(blockDim.x) / WAVE : 1;
     const int wid = MODE == 2 ? __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / WAVE) : 0;
     const int lane = MODE == 2 ? static_cast<int>(threadIdx.x) % WAVE : static_cast<int>(threadIdx.x);
-    const int blk = MODE == 0 ? static_cast<int>(blockIdx.x) : xcd_block(blockIdx.x, g.nblk);
+    const int blk = MODE == 0 || (MODE == 1 && !g.want_back) ? static_cast<int>(blockIdx.x)
+                                                             : xcd_block(blockIdx.x, g.nblk);
     const int grp = MODE == 2 ? blk * nw + wid : blk;
     const int ngrp = MODE == 2 ? (g.N + apw - 1) / apw : g.nblk;
     const bool grp_live = MODE != 2 || grp < ngrp;
