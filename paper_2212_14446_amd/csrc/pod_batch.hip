@@ -3,7 +3,8 @@
 // global descriptors G = sum_i D_i of each cell and their derivatives
 // dG/dr_n (Sec. II.G, eqs. (26c), (24c), product rule for the 2- and 4-body
 // terms), in FP64.  Three kernels over the cells in order of decreasing pair
-// count (batches beyond 2 GB of scratch, or what the device has, in several rounds of them):
+// count (batches beyond 2 GB of scratch, or what the device has, in several
+// rounds of them):
 //   1. pair records: (rhat, 1/r) per pair and, per radial index, (R_m, R'_m),
 //      in slot-major order (see BArgs);
 //   2. forward: lanes (atom, m) accumulate the atomic-basis rows (eq. (24b)),
@@ -37,8 +38,8 @@
 // of 64 items from a counter, highest degree first.
 //
 // 2,000 cells of 2 to 250 atoms (250,505 atoms, 6.6 M pairs, 17 columns per
-// radial index): 6.85 -> 3.50 ms (records 0.30, basis 0.62, dG/dR 2.6), 200
-// cells 1.69 -> 0.43 ms, against one pass over all 35 monomials for every
+// radial index): 6.85 -> 3.78 ms of kernels (records 0.30, basis 0.62, dG/dR
+// 2.8), 200 cells 1.69 -> 0.42 ms, against one pass over all 35 monomials for every
 // column in a persistent kernel.  dG/dR is held by the record loads and the
 // LDS atomics together (without either 2.0, without the polynomials 2.3 ms).
 // The same product on the FP64 matrix cores (15 Jacobian rows as one tile of
@@ -472,8 +473,10 @@ __global__ __launch_bounds__(BASIS_THREADS) void batch_basis_kernel(BArgs g) {
         for (int k = tid; k < M; k += BASIS_THREADS) g.G[static_cast<size_t>(c) * M + k] = sG[k];
 }
 
-// ---- 3. dG/dR: one workgroup per (cell, radial index) item ----
-// Angular degree up to 4 fits 128 registers (16 wavefronts per compute unit).
+// ---- 3. dG/dR: one workgroup per item (cell, radial index, chunk) ----
+// Threads per workgroup at most: three wavefronts per SIMD up to degree 4 (168
+// registers), two above (256; degree 6 spills 380 bytes a lane, and 1,936 in the
+// former kernel).  By default two or more workgroups of 256 share a compute unit where the LDS allows.
 constexpr int deriv_threads(int PA) { return PA <= 4 ? 768 : 512; }
 
 template <int PA>

@@ -18,7 +18,7 @@ namespace pod {
 // 65.9 / 45.5, 1,024 66.5 / 85.5; K = 7, P3 = 6: 128 atoms 84.7 / 23.1.
 // Descriptors, degree 4: 128 atoms 16.7 / 10.5 us, 1,024 16.9 / 13.1, 2,000 17.2
 // / 23.9.  (About 23 us of a call are the caller's side.)
-inline int small_max(int PA) { return PA <= 4 ? 1024 : 512; }
+constexpr int small_max(int PA) { return PA <= 4 ? 1024 : 512; }
 
 // Threads per workgroup: 256 while the chip holds every atom at once (two
 // workgroups per compute unit), 128 above (1,024 atoms: 35.0 against 28.4 us).

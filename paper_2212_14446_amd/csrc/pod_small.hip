@@ -399,8 +399,13 @@ hipError_t launch_pa(const WideArgs<T>& a, int mode, bool fast, hipStream_t st) 
             else hipLaunchKernelGGL((small_kernel<T, PA, 1, false, ST>), grid, dim3(ST), lds, st, a);
         }
     };
-    if (a.N <= SMALL_WIDE_N) go(std::integral_constant<int, 256>{});
-    else go(std::integral_constant<int, 128>{});
+    if constexpr (small_max(PA) > SMALL_WIDE_N) {
+        if (a.N > SMALL_WIDE_N) {
+            go(std::integral_constant<int, 128>{});
+            return hipGetLastError();
+        }
+    }
+    go(std::integral_constant<int, 256>{});
     return hipGetLastError();
 }
 
