@@ -80,7 +80,7 @@ struct KArgs {
     int want_back;     // adjoint rows requested (forces or virial)
     const net::Packed* netw;  // mode 2: network weights (pod_net.h)
     int n_net;                // mode 2: network inputs, descriptor columns 1 .. n_net
-    int nblk;                 // workgroups (modes 1 and 2)
+    int nblk;                 // workgroups (modes 1 to 3)
     int* err;
 };
 
@@ -150,7 +150,8 @@ __host__ __device__ inline AtomLds atom_lds_layout(int K, int NA, int M, size_t 
 // any work (0.3 us a kernel; 15,840 atoms 59.4 -> 58.8 us).  Descriptors and
 // energies alone keep the plain order: nothing that they write is read again
 // (energies of 432,000 atoms, K = 4, degree 3, FP32 194 us renumbered / 180; 128,000
-// atoms, K = 7, degree 6, FP64, 84 pairs 795 / 783; others the same).
+// atoms, K = 7, degree 6, FP64, 84 pairs 795 / 783; others the same).  The order is
+// the instance's: chosen by an argument it cost every energy call 0.3 us.
 __device__ __forceinline__ int xcd_block(int i, int n) {
     constexpr int NX = 8;
     const int x = i % NX, k = i / NX;
@@ -161,6 +162,8 @@ __device__ __forceinline__ int xcd_block(int i, int n) {
 // One workgroup = one wavefront = APW = 64 / K atoms.  Neighbour slots are
 // processed K at a time per atom ("rounds"); in a round, lane (a, s)
 // evaluates slot s of atom a.
+// MODE 0: descriptors.  1: energy and what the pair kernel needs.  2: the same
+// with the network in place of the 4-body term.  3: energy alone.
 template <typename T, int PA, int MODE, bool FAST>
 __device__ __forceinline__ void atom_body(const KArgs<T>& g) {
     constexpr MonoTable<PA> mt{};
@@ -182,8 +185,8 @@ __device__ __forceinline__ void atom_body(const KArgs<T>& g) {
     const int nw = MODE == 2 ? static_cast<int>(blockDim.x) / WAVE : 1;
     const int wid = MODE == 2 ? __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / WAVE) : 0;
     const int lane = MODE == 2 ? static_cast<int>(threadIdx.x) % WAVE : static_cast<int>(threadIdx.x);
-    const int blk = MODE == 0 || (MODE == 1 && !g.want_back) ? static_cast<int>(blockIdx.x)
-                                                             : xcd_block(blockIdx.x, g.nblk);
+    constexpr bool HAND_ON = MODE == 1 || MODE == 2;   // rows, centres and pair vectors for the pair kernel
+    const int blk = HAND_ON ? xcd_block(blockIdx.x, g.nblk) : static_cast<int>(blockIdx.x);
     const int grp = MODE == 2 ? blk * nw + wid : blk;
     const int ngrp = MODE == 2 ? (g.N + apw - 1) / apw : g.nblk;
     const bool grp_live = MODE != 2 || grp < ngrp;
@@ -232,7 +235,7 @@ __device__ __forceinline__ void atom_body(const KArgs<T>& g) {
                 i1 = slot_index(g, act && slot + 2 * K < cnt, beg + slot + 2 * K);
                 T d[3], r;
                 const bool ok = slot_geometry<T>(g, live, ic, pc, pi, eb, d, r);
-                if constexpr (MODE != 0) {
+                if constexpr (HAND_ON) {
                     // centre atom and pair vector for the pair kernel (an empty
                     // slot writes the spare entry P)
                     const int pw = live ? beg + slot : g.P;
@@ -506,6 +509,8 @@ __device__ __forceinline__ void atom_body(const KArgs<T>& g) {
             for (int mu = 0; mu < NA; ++mu)
                 abrow[mu] = T(2 * mt.mult[mu]) * eff3[mt.deg[mu]] * abrow[mu] + (mu == 0 ? eff2 : T(0));
         }
+    } else if constexpr (!HAND_ON) {
+        // energy alone: no rows
     } else if constexpr (AB_LDS) {
         if (act) {
             T* abrow = sT + al * AST + m * NA;
@@ -556,7 +561,7 @@ __device__ __forceinline__ void atom_body(const KArgs<T>& g) {
         const double eb = wave_sum(ei);
         if (lane == 0 && grp_live) g.part[grp] = eb;
     }
-    if (!g.want_back) return;
+    if (!HAND_ON || !g.want_back) return;
 
     // ---------------- adjoint rows to memory ----------------
     // rows dE_i/dB_{i k .} of the workgroup's atoms, [atom][k][mu] (K * NA
@@ -1325,9 +1330,12 @@ int energy_forces_run(pod_handle* h, char* scratch, double* facc, int N, int P, 
         const size_t pw = lds_bytes(h->K, h->PA, sizeof(T), h->M);
         const int nw = MODE == 2 ? net_waves(h->K, pw) : 1;
         const size_t lds = nw * pw + (MODE == 2 ? net_tiles(nw, apw) * NET_LDS : 0);
-        a.nblk = (nblk + nw - 1) / nw;
+        const int nwg = (nblk + nw - 1) / nw;
+        a.nblk = nwg;
         timing_begin(h, 1);
-        const hipError_t e = dispatch_pa<T, MODE>(h->PA, a, h->std_ok != 0, a.nblk, nw * WAVE, lds, h->stream);
+        const hipError_t e =
+            MODE == 1 && !back ? dispatch_pa<T, 3>(h->PA, a, h->std_ok != 0, nwg, WAVE, lds, h->stream)
+                               : dispatch_pa<T, MODE>(h->PA, a, h->std_ok != 0, nwg, nw * WAVE, lds, h->stream);
         timing_end(h, 1);
         if (e != hipSuccess) return POD_EHIP;
     }
