@@ -228,7 +228,7 @@ def roofline(w, r, dtype, traffic=True):
 @on_stream
 def run_batch(steps, warmup):
     """Batched assembly of 2,000 cells (2..250 atoms; BCC/FCC/A15/liquid):
-    D, G and dG/dR per cell in one launch, FP64, autotuned launch shape."""
+    D, G and dG/dR per cell in one call, FP64, autotuned launch shape."""
     import torch
 
     from paper_2212_14446_amd import autotune as at, flops as fl, pod, workloads as wl
