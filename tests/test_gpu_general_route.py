@@ -50,6 +50,12 @@ def _errors(case, dtype):
         errs[f"E {path}"] = abs(o["E"][0] / copies - o_ref["E"]) / abs(o_ref["E"])
         for k in ("W", "G"):
             errs[f"{k} {path}"] = relerr(o[k] / copies, o_ref[k])
+    # energies alone: an instance of their own
+    o = {k: cpu(v) for k, v in m.energy_forces(big, case.cell, nb, case.c, forces=False, virial=False).items()
+         if v is not None}
+    errs["E_atom alone"] = max(relerr(x, o_ref["E_atom"]) for x in o["E_atom"].reshape(copies, N))
+    errs["E alone"] = abs(o["E"][0] / copies - o_ref["E"]) / abs(o_ref["E"])
+    errs["G alone"] = relerr(o["G"] / copies, o_ref["G"])
     say(f"[gpu] general route {case.name} {dtype} N={copies * N}: " + " ".join(f"{k}={v:.1e}" for k, v in errs.items()))
     return errs
 
